@@ -1433,6 +1433,8 @@ int seed_tile_f64_real(void *a0, int64_t L2, int Bt, const int32_t *sites, doubl
     return CBDG_OK;
 }
 
+static int64_t moments_bytes(const cbdg_op *op, int64_t tile, int precision, bool doubling);
+
 // Direct: steps n = 1 .. N-1, each capturing moment n of every vector.
 // Doubling: steps n = 1 .. ceil((N-1)/2); step 1 captures moment 1 and every
 // step's partial sums give moments 2n-1 and 2n.  Real uniform operators take
@@ -1542,10 +1544,10 @@ static int run_moments(const cbdg_op *op, const int32_t *sites, int64_t n_start,
         }
         return bound_moments(mee, mhe, (int64_t)Bt * N, false, false, moment_limit(f32), st);
     };
-    if (n_start > 0 && vc_tile((int)std::min<int64_t>(tile, n_start))) {
-        int rc = launch_vc_coef(onsite, vc_coef, op->Lx, f32, L2, st);
-        if (rc) return rc;
-    }
+    // where the workspace holds packed coefficients: of the pipelined recursion
+    // (byte offset and width, or -1), of the vector-contiguous passes
+    [[maybe_unused]] int64_t pipe_coef = -1;
+    [[maybe_unused]] bool have_vc_coef = false;
     for (int64_t t0 = 0; t0 < n_start; t0 += tile) {
         const int Bt = (int)std::min<int64_t>(tile, n_start - t0);
         const int64_t Bp = lane_stride(Bt);
@@ -1553,12 +1555,27 @@ static int run_moments(const cbdg_op *op, const int32_t *sites, int64_t n_start,
         double *mhe = mu_he + t0 * N * he_mult;
         const int32_t *ts = sites + t0;
         if constexpr (!C) {
+            if (!vc_out && !nb_ee && doubling) {
+                const int64_t room = moments_bytes(op, Bt, f32 ? CBDG_FP32_ACC64 : CBDG_FP64, true);
+                const PipePlan pp = pipe_plan(op, Bt, f32, room);
+                if (pp.W) {
+                    int rc = run_pipe(op, pp, f32, ts, Bt, N, ws, mee, mhe, pipe_coef != pp.coef_at * 16 + pp.W, st);
+                    if (rc) return rc;
+                    pipe_coef = pp.coef_at * 16 + pp.W;
+                    have_vc_coef = false;
+                    continue;
+                }
+            }
             if (vc_tile(Bt)) {
-                int rc = run_tile_vc(Bt, Bp, ts, mee, mhe);
-                if (rc) return rc;
+                int rc = have_vc_coef ? CBDG_OK : launch_vc_coef(onsite, vc_coef, op->Lx, f32, L2, st);
+                if (rc || (rc = run_tile_vc(Bt, Bp, ts, mee, mhe))) return rc;
+                pipe_coef = -1;
+                have_vc_coef = true;
                 continue;
             }
         }
+        pipe_coef = -1;
+        have_vc_coef = false;
         const int64_t nz = L2 * Bp;
         const unsigned zgrid = (unsigned)std::min<int64_t>(ceil_div(nz, kBlock), 8192);
         for (int i = 0; i < nbuf; ++i) {
@@ -1719,6 +1736,8 @@ static int resolve_algorithm(const cbdg_op *op, int32_t algorithm, int32_t N, co
     }
 }
 
+namespace cbdg {
+
 static int64_t doubling_partial_bytes(const cbdg_op *op, int tile, int precision)
 {
     const bool cplx = op->scalar == CBDG_COMPLEX;
@@ -1753,7 +1772,13 @@ static size_t tile_buffer_bytes(const cbdg_op *op, int64_t tile, int precision)
     return nbuf * (size_t)op->L2 * (size_t)lane_stride(tile) * pair_bytes(op->scalar, precision);
 }
 
-namespace cbdg {
+// Workspace of a moments call in tiles of `tile` vectors.
+static int64_t moments_bytes(const cbdg_op *op, int64_t tile, int precision, bool doubling)
+{
+    size_t n = tile_buffer_bytes(op, tile, precision) + kConeDoubles * sizeof(double);
+    if (doubling) n += (size_t)doubling_partial_bytes(op, (int)tile, precision) + vc_coef_bytes(op, precision);
+    return (int64_t)n;
+}
 
 bool vc_adjoint_supported(const cbdg_op *op)
 {
@@ -1789,8 +1814,7 @@ extern "C" int cbdg_moments_workspace_size(const cbdg_op *op, int32_t tile, int3
     // sized for any N: the partials are included whenever doubling may run
     int rc = resolve_algorithm(op, algorithm, 3, "moments_workspace_size", &doubling);
     if (rc) return rc;
-    *bytes = tile_buffer_bytes(op, tile, precision) + kConeDoubles * sizeof(double);
-    if (doubling) *bytes += (size_t)doubling_partial_bytes(op, tile, precision) + vc_coef_bytes(op, precision);
+    *bytes = (size_t)moments_bytes(op, tile, precision, doubling);
     return CBDG_OK;
 }
 
@@ -1813,8 +1837,7 @@ extern "C" int cbdg_chebyshev_moments(const cbdg_op *op, const int32_t *start_si
     if (!start_sites || !mu_ee || !mu_he || !workspace)
         return fail(CBDG_EINVAL, "chebyshev_moments: start_sites, mu_ee, mu_he and workspace must not be NULL");
     const int64_t eff_tile = std::min<int64_t>(tile, n_start);
-    size_t need = tile_buffer_bytes(op, eff_tile, precision) + kConeDoubles * sizeof(double);
-    if (doubling) need += (size_t)doubling_partial_bytes(op, (int)eff_tile, precision) + vc_coef_bytes(op, precision);
+    const size_t need = (size_t)moments_bytes(op, eff_tile, precision, doubling);
     if (workspace_bytes < need)
         return fail(CBDG_EINVAL, "chebyshev_moments: workspace of %zu bytes is smaller than the %zu needed",
                     workspace_bytes, need);

@@ -152,6 +152,42 @@ int vc_forward_last(const cbdg_op *op, const int32_t *sites, int Bt, int N, void
                     hipStream_t st, void **last, void **spare, const void **coef);
 bool vc_adjoint_supported(const cbdg_op *op);
 
+// The pipelined recursion (vpipe.hpp): passes p = 0 .. n_pass-1 of L steps
+// each over a tile stored vector by vector, rows of rowp pairs (nl lanes of W
+// columns, each lane's pairs in 16-byte chunks, chunk j of lane l at chunk
+// j*nl + l of the row).  Pass p takes steps n0 + pL .. n0 + pL + L - 1 from
+// a_{n-2} in x and a_{n-1} in y to xo and yo (x and y themselves, or another
+// pair that is exchanged with them after every pass).
+struct PipeArgs {
+    void *x, *y, *xo, *yo;
+    const void *coef;    // (2 de, 2 Delta/a) per site in the same row layout
+    const void *onsite;  // OnSite<T>[L2]
+    double th;           // t/a
+    double lim;          // moments beyond it are stored as NaN
+    int Lx, Ly, bcx, bcy;
+    int W, nl, rowp;
+    int64_t Dv;          // pairs per vector, Ly * rowp
+    int Bt, N;
+    int n0, n_pass, n_segs;
+    int seed;            // the launch writes a_0, a_1 and moments 0 .. 2 itself
+    const int32_t *sites;
+    double *mu_ee, *mu_he;
+    double *part;        // n_segs > 1: doubling sums [L][n_segs][3][Bt]
+};
+
+// Shape of the pipelined recursion for a tile of Bt vectors (W = 0: not for
+// this operator) and its workspace: nbuf buffers of Bt vectors, the packed
+// coefficients at byte coef_at, the segments' sums at part_at.
+struct PipePlan {
+    int W, nl, rowp, L, segs, nbuf;
+    int64_t Dv, coef_at, part_at, bytes;
+};
+// limit: bytes of workspace it may take.
+PipePlan pipe_plan(const cbdg_op *op, int Bt, bool f32, int64_t limit);
+// The moments of a tile; coef: the coefficients at ws + coef_at are to be written.
+int run_pipe(const cbdg_op *op, const PipePlan &p, bool f32, const int32_t *sites, int Bt, int N, void *ws, double *mu_ee,
+             double *mu_he, bool coef, hipStream_t st);
+
 // a_0 (its whole start row) and the zeroth moments of a tile
 int launch_vc_seed(void *a0, int64_t Dv, int Lx, bool f32, int Bt, int64_t L2, const int32_t *sites, double *mu_ee,
                    double *mu_he, int N, hipStream_t st);

@@ -1,0 +1,223 @@
+// Host side of the pipelined recursion: which tiles take it, its coefficients
+// and launches, and the reduction of the row segments' sums.
+#include "vpipe.hpp"
+
+#include <algorithm>
+
+namespace cbdg {
+
+int launch_pipe_f64_11(const PipeArgs &A, hipStream_t st);
+int launch_pipe_f64_21(const PipeArgs &A, hipStream_t st);
+int launch_pipe_f64_31(const PipeArgs &A, hipStream_t st);
+int launch_pipe_f64_41(const PipeArgs &A, hipStream_t st);
+int launch_pipe_f64_32(const PipeArgs &A, hipStream_t st);
+int launch_pipe_f64_42(const PipeArgs &A, hipStream_t st);
+int launch_pipe_f32_11(const PipeArgs &A, hipStream_t st);
+int launch_pipe_f32_21(const PipeArgs &A, hipStream_t st);
+int launch_pipe_f32_41(const PipeArgs &A, hipStream_t st);
+int launch_pipe_f32_42(const PipeArgs &A, hipStream_t st);
+
+// The shapes that are built: lanes of W columns, C wavefronts per row, in the
+// order of the widest row they take.
+struct PipeWidth {
+    int W, C, L, per_cu;  // columns, wavefronts per row, steps of a pass, workgroups per CU
+    int (*launch)(const PipeArgs &, hipStream_t);
+};
+template <typename T, int W, int C>
+static constexpr PipeWidth pipe_width(int (*launch)(const PipeArgs &, hipStream_t))
+{
+    using Sh = PipeShape<T, W, C>;
+    return PipeWidth{W, C, Sh::K * Sh::S, 4 * Sh::waves / (Sh::S * C), launch};
+}
+static const PipeWidth kWidths64[] = {
+    pipe_width<double, 1, 1>(launch_pipe_f64_11),
+    pipe_width<double, 2, 1>(launch_pipe_f64_21),
+    pipe_width<double, 3, 1>(launch_pipe_f64_31),
+    pipe_width<double, 4, 1>(launch_pipe_f64_41),
+    pipe_width<double, 3, 2>(launch_pipe_f64_32),
+    pipe_width<double, 4, 2>(launch_pipe_f64_42),
+};
+static const PipeWidth kWidths32[] = {
+    pipe_width<float, 1, 1>(launch_pipe_f32_11),
+    pipe_width<float, 2, 1>(launch_pipe_f32_21),
+    pipe_width<float, 4, 1>(launch_pipe_f32_41),
+    pipe_width<float, 4, 2>(launch_pipe_f32_42),
+};
+
+template <typename F>
+static const PipeWidth *find_width(bool f32, F &&fits)
+{
+    const PipeWidth *w = f32 ? kWidths32 : kWidths64;
+    const int n = f32 ? (int)(sizeof(kWidths32) / sizeof(*w)) : (int)(sizeof(kWidths64) / sizeof(*w));
+    for (int i = 0; i < n; ++i)
+        if (fits(w[i])) return &w[i];
+    return nullptr;
+}
+
+static int launch_pipe(const PipeArgs &A, bool f32, hipStream_t st)
+{
+    const PipeWidth *w = find_width(f32, [&](const PipeWidth &v) { return v.W == A.W && kWave * v.W * v.C >= A.Lx; });
+    if (!w) return fail(CBDG_EUNSUPPORTED, "pipelined recursion: no width for Lx = %d", A.Lx);
+    return w->launch(A, st);
+}
+
+static bool plan_width(const cbdg_op *op, const PipeWidth &w, int Bt, bool f32, bool cut, int64_t limit, PipePlan &p)
+{
+    if (kWave * w.W * w.C < op->Lx) return false;
+    p = PipePlan{};
+    p.W = w.W;
+    p.L = w.L;
+    p.nl = (int)ceil_div(op->Lx, w.W);
+    p.rowp = p.nl * (int)round_up(w.W, f32 ? 2 : 1);
+    // Row segments per vector, by the trips the slowest workgroup takes for a
+    // pass.  One segment: the passes of a vector follow each other without a
+    // gap, each taking its rows and those between two passes.  Segments: one
+    // launch per pass; each fills and empties the pipeline and recomputes L
+    // rows at either end, and the launches of a pass cost about 20 trips.
+    // With one workgroup on a CU instead of two a trip is a little shorter
+    // (256x256, N = 512, ms by segments; 64 vectors 1: 3.45, 2: 3.06, 4: 2.43,
+    // 6: 4.11; 128 vectors 1: 3.52, 2: 3.13, 4: 4.77).
+    const int rows = op->Ly, lag = 2 * p.L + 12, wrap = op->bc_y ? 2 * p.L : 0;
+    auto rounds = [&](int64_t n) {
+        return ceil_div(n, 256 * (int64_t)w.per_cu) - (w.per_cu > 1 && (n - 1) % 512 < 256 ? 0.1 : 0.0);
+    };
+    p.segs = 1;
+    double best = rounds(Bt) * (std::max(rows + 12, p.L + 16) + wrap);
+    for (int k = 2; cut && k <= rows / 4 && (int64_t)k * Bt <= 1024; ++k) {
+        const double t = rounds((int64_t)k * Bt) * (ceil_div(rows, k) + 2 * p.L + lag) + 20;
+        if (t < 0.95 * best) { best = t; p.segs = k; }
+    }
+    p.nbuf = p.segs > 1 || op->bc_y ? 4 : 2;
+    const int64_t pair = f32 ? 8 : 16;
+    p.Dv = (int64_t)op->Ly * p.rowp;
+    if (p.Dv * pair > INT32_MAX) return false;
+    p.coef_at = p.nbuf * p.Dv * Bt * pair;
+    p.part_at = round_up(p.coef_at + p.Dv * pair, 256);
+    p.bytes = p.part_at + (p.segs > 1 ? (int64_t)p.L * p.segs * 3 * Bt * 8 : 0);
+    return p.bytes <= limit;
+}
+
+PipePlan pipe_plan(const cbdg_op *op, int Bt, bool f32, int64_t limit)
+{
+    PipePlan p{};
+    if (op->scalar != CBDG_REAL || op->general || op->bounds.b != 0.0) return p;
+    // Where the seven-step passes apply too they keep two ranges.  A short
+    // periodic lattice is run through L rows more at either end on every pass
+    // here, through six there (1024 vectors, N = 256, us: 256x24 2017 there,
+    // 3179 here; 128x24 2249 / 2721; 128x64 2164 / 2234, 256x128 6600 / 6551).
+    // A quarter to a half of the workgroups a launch can hold: there row
+    // segments fill the GPU at less recomputation (N = 256, us: 128x256, 128
+    // vectors 1022 / 1132, 32 vectors 1010 / 810; FP32 256x256, 64 vectors 953
+    // / 1231, 256 vectors 1856 / 2026, 512 vectors 3560 / 2870).
+    const int vw = vc_width(op->Lx, f32);
+    if (vw > 0 && op->bc_y && op->Ly <= 16 * (vw + 1)) return p;
+    if (vw == (f32 ? 4 : 2) && Bt > 32 && Bt <= (f32 ? 256 : 128)) return p;
+    // FP32 rows of up to 40 sites fill a third of a wavefront or less here (two
+    // sites a lane): the vector-major passes keep the periodic ones (24x128,
+    // 1024 vectors, N = 256: 4317 us against 7066).
+    if (f32 && op->bc_y && op->Lx <= 40) return p;
+    const PipeWidth *w = nullptr;
+    for (int cut = 1; cut >= 0 && !w; --cut)
+        w = find_width(f32, [&](const PipeWidth &v) { return plan_width(op, v, Bt, f32, cut != 0, limit, p); });
+    if (!w) p.W = 0;
+    return p;
+}
+
+// scale * (de, Delta/a) of every site in the passes' row layout, zero past Lx
+template <typename T>
+__global__ void k_pipe_coef(const OnSite<T> *__restrict__ ons, typename Storage<T, false>::type *__restrict__ pc, int Lx,
+                            int W, int nl, int rowp, int64_t Dv, T scale)
+{
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < Dv; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t y = i / rowp;
+        const int pos = (int)(i - y * rowp), ch = pos / kPer<T>;
+        const int k = ch / nl * kPer<T> + pos % kPer<T>, x = ch % nl * W + k;
+        typename Storage<T, false>::type c{T(0), T(0)};
+        if (k < W && x < Lx) {
+            const OnSite<T> o = ons[y * Lx + x];
+            c = typename Storage<T, false>::type{scale * o.de, scale * o.dr};
+        }
+        pc[i] = c;
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_pipe_seed(PipeArgs A)
+{
+    pipe_seed<T>(A, blockIdx.x, A.sites[blockIdx.x], threadIdx.x, kBlock);
+}
+
+// Moments of the steps n0 .. n0+L-1 from the segments' sums, added in order:
+// one thread per (step, vector).
+template <typename T>
+__global__ void k_pipe_reduce(PipeArgs A, int L)
+{
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= (int64_t)L * A.Bt) return;
+    const int lev = (int)(i / A.Bt), b = (int)(i - (int64_t)lev * A.Bt);
+    const int32_t si = A.sites[b];
+    if (si < 0 || si >= A.Lx * A.Ly) return;
+    double s[3] = {0.0, 0.0, 0.0};
+    for (int g = 0; g < A.n_segs; ++g)
+        for (int k = 0; k < 3; ++k) s[k] += A.part[(((int64_t)lev * A.n_segs + g) * 3 + k) * A.Bt + b];
+    const OnSite<T> o = reinterpret_cast<const OnSite<T> *>(A.onsite)[si];
+    pipe_moments(A, (int64_t)b * A.N, A.n0 + lev, s, (double)o.de, (double)o.dr);
+}
+
+template <typename T>
+static int run_pipe_t(const cbdg_op *op, const PipePlan &p, const int32_t *sites, int Bt, int N, char *ws, double *mu_ee,
+                      double *mu_he, bool coef, hipStream_t st)
+{
+    using V = typename Storage<T, false>::type;
+    constexpr bool f32 = sizeof(T) == 4;
+    V *buf = reinterpret_cast<V *>(ws);
+    PipeArgs A{};
+    const int64_t one = p.Dv * Bt;
+    A.x = buf; A.y = buf + one;
+    A.xo = p.nbuf == 4 ? buf + 2 * one : buf;
+    A.yo = p.nbuf == 4 ? buf + 3 * one : buf + one;
+    A.coef = ws + p.coef_at;
+    A.part = reinterpret_cast<double *>(ws + p.part_at);
+    A.onsite = f32 ? (const void *)op->onsite32 : (const void *)op->onsite64;
+    A.th = op->t / op->bounds.a;
+    A.lim = moment_limit(f32);
+    A.Lx = op->Lx; A.Ly = op->Ly; A.bcx = op->bc_x; A.bcy = op->bc_y;
+    A.W = p.W; A.nl = p.nl; A.rowp = p.rowp; A.Dv = p.Dv;
+    A.Bt = Bt; A.N = N; A.n_segs = p.segs;
+    A.sites = sites; A.mu_ee = mu_ee; A.mu_he = mu_he;
+    if (coef) {
+        hipLaunchKernelGGL((k_pipe_coef<T>), dim3((unsigned)std::min<int64_t>(ceil_div(p.Dv, kBlock), 4096)), dim3(kBlock),
+                           0, st, reinterpret_cast<const OnSite<T> *>(A.onsite), reinterpret_cast<V *>(ws + p.coef_at),
+                           A.Lx, A.W, A.nl, A.rowp, A.Dv, T(pipe_folds(A.Lx, f32) ? 2 : 1));
+        CBDG_CHECK_LAUNCH("k_pipe_coef");
+    }
+    const int steps = N / 2 - 1, passes = (int)ceil_div(steps, p.L);
+    A.n0 = 2;
+    if (p.segs == 1 && steps > 0) {
+        A.seed = 1;
+        A.n_pass = passes;
+        return launch_pipe(A, f32, st);
+    }
+    hipLaunchKernelGGL((k_pipe_seed<T>), dim3(Bt), dim3(kBlock), 0, st, A);
+    CBDG_CHECK_LAUNCH("k_pipe_seed");
+    A.n_pass = 1;
+    for (int i = 0; i < passes; ++i) {
+        A.n0 = 2 + i * p.L;
+        int rc = launch_pipe(A, f32, st);
+        if (rc) return rc;
+        hipLaunchKernelGGL((k_pipe_reduce<T>), dim3((unsigned)ceil_div((int64_t)p.L * Bt, kBlock)), dim3(kBlock), 0, st, A, p.L);
+        CBDG_CHECK_LAUNCH("k_pipe_reduce");
+        std::swap(A.x, A.xo);
+        std::swap(A.y, A.yo);
+    }
+    return CBDG_OK;
+}
+
+int run_pipe(const cbdg_op *op, const PipePlan &p, bool f32, const int32_t *sites, int Bt, int N, void *ws, double *mu_ee,
+             double *mu_he, bool coef, hipStream_t st)
+{
+    return f32 ? run_pipe_t<float>(op, p, sites, Bt, N, reinterpret_cast<char *>(ws), mu_ee, mu_he, coef, st)
+               : run_pipe_t<double>(op, p, sites, Bt, N, reinterpret_cast<char *>(ws), mu_ee, mu_he, coef, st);
+}
+
+}  // namespace cbdg

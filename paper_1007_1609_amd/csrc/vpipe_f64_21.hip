@@ -1,0 +1,8 @@
+// The pipelined recursion's FP64 kernels for lanes of 2 columns.
+#include "vpipe.hpp"
+
+namespace cbdg {
+
+int launch_pipe_f64_21(const PipeArgs &A, hipStream_t st) { return launch_pipe_w<double, 2, 1>(A, st); }
+
+}  // namespace cbdg
