@@ -1,0 +1,15 @@
+// The general row pipeline's kernels: complex, per-bond operators, FP64.
+#include "gpipe.hpp"
+
+namespace cbdg {
+
+int launch_gpipe_f64_cg(const GPipeArgs &G, int grid, hipStream_t st)
+{
+    switch (G.P.W) {
+    case 1: return launch_gpipe_w<double, true, true, 1>(G, grid, st);
+    case 2: return launch_gpipe_w<double, true, true, 2>(G, grid, st);
+    default: return fail(CBDG_EUNSUPPORTED, "row pipeline: no width for Lx = %d", G.P.Lx);
+    }
+}
+
+}  // namespace cbdg

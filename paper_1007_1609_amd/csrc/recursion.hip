@@ -1548,6 +1548,7 @@ static int run_moments(const cbdg_op *op, const int32_t *sites, int64_t n_start,
     // (byte offset and width, or -1), of the vector-contiguous passes
     [[maybe_unused]] int64_t pipe_coef = -1;
     [[maybe_unused]] bool have_vc_coef = false;
+    bool have_records = false;  // of the general row pipeline, at its start
     for (int64_t t0 = 0; t0 < n_start; t0 += tile) {
         const int Bt = (int)std::min<int64_t>(tile, n_start - t0);
         const int64_t Bp = lane_stride(Bt);
@@ -1576,6 +1577,18 @@ static int run_moments(const cbdg_op *op, const int32_t *sites, int64_t n_start,
         }
         pipe_coef = -1;
         have_vc_coef = false;
+        if (nb_ee || doubling) {
+            const int64_t room = nb_ee ? 2 * L2 * Bp * (int64_t)sizeof(S) : moments_bytes(op, Bt, f32 ? CBDG_FP32_ACC64 : CBDG_FP64, true);
+            const GPipePlan gp = gpipe_plan(op, Bt, f32, nb_ee != nullptr, room);
+            if (gp.W) {
+                int rc = run_gpipe(op, gp, f32, ts, Bt, N, ws, mee, mhe, nb_ee ? nb_ee + t0 * 4 * N * he_mult : nullptr,
+                                   nb_ee ? nb_he + t0 * 4 * N * he_mult : nullptr, !have_records, st);
+                if (rc) return rc;
+                have_records = true;
+                continue;
+            }
+        }
+        have_records = false;
         const int64_t nz = L2 * Bp;
         const unsigned zgrid = (unsigned)std::min<int64_t>(ceil_div(nz, kBlock), 8192);
         for (int i = 0; i < nbuf; ++i) {

@@ -155,11 +155,13 @@ bool vc_adjoint_supported(const cbdg_op *op);
 // The pipelined recursion (vpipe.hpp): passes p = 0 .. n_pass-1 of L steps
 // each over a tile stored vector by vector, rows of rowp pairs (nl lanes of W
 // columns, each lane's pairs in 16-byte chunks, chunk j of lane l at chunk
-// j*nl + l of the row).  Pass p takes steps n0 + pL .. n0 + pL + L - 1 from
-// a_{n-2} in x and a_{n-1} in y to xo and yo (x and y themselves, or another
-// pair that is exchanged with them after every pass).
+// j*nl + l of the row).  Buffers of `one` bytes hold the tile's a_{n-2} and
+// a_{n-1} (a pair); pass p takes steps n0 + pL .. n0 + pL + L - 1 from pair
+// (p + cur) & flip to pair (p + 1 + cur) & flip.
 struct PipeArgs {
-    void *x, *y, *xo, *yo;
+    char *buf;
+    int64_t one;
+    int flip, cur;
     const void *coef;    // (2 de, 2 Delta/a) per site in the same row layout
     const void *onsite;  // OnSite<T>[L2]
     double th;           // t/a
@@ -187,6 +189,20 @@ PipePlan pipe_plan(const cbdg_op *op, int Bt, bool f32, int64_t limit);
 // The moments of a tile; coef: the coefficients at ws + coef_at are to be written.
 int run_pipe(const cbdg_op *op, const PipePlan &p, bool f32, const int32_t *sites, int Bt, int N, void *ws, double *mu_ee,
              double *mu_he, bool coef, hipStream_t st);
+
+// The general row pipeline (gpipe.hpp): complex and per-bond operators under
+// doubling, every operator's neighbour moments (direct).  W = 0: not for this
+// tile.  The workspace holds the records, then nbuf buffers of `grid` vectors.
+struct GPipePlan {
+    int W, nl, recs, grid, nbuf;
+    int64_t Dv, buf_at;
+};
+GPipePlan gpipe_plan(const cbdg_op *op, int Bt, bool f32, bool direct, int64_t room);
+int run_gpipe(const cbdg_op *op, const GPipePlan &p, bool f32, const int32_t *sites, int Bt, int N, void *ws, double *mu_ee,
+              double *mu_he, double *nb_ee, double *nb_he, bool records, hipStream_t st);
+
+// The sites' records in rows of nl lanes of W columns, recs values per row.
+int launch_gpipe_records(const cbdg_op *op, int W, int nl, int recs, bool f32, void *ws, hipStream_t st);
 
 // a_0 (its whole start row) and the zeroth moments of a tile
 int launch_vc_seed(void *a0, int64_t Dv, int Lx, bool f32, int Bt, int64_t L2, const int32_t *sites, double *mu_ee,

@@ -170,12 +170,10 @@ static int run_pipe_t(const cbdg_op *op, const PipePlan &p, const int32_t *sites
 {
     using V = typename Storage<T, false>::type;
     constexpr bool f32 = sizeof(T) == 4;
-    V *buf = reinterpret_cast<V *>(ws);
     PipeArgs A{};
-    const int64_t one = p.Dv * Bt;
-    A.x = buf; A.y = buf + one;
-    A.xo = p.nbuf == 4 ? buf + 2 * one : buf;
-    A.yo = p.nbuf == 4 ? buf + 3 * one : buf + one;
+    A.buf = ws;
+    A.one = p.Dv * Bt * (int64_t)sizeof(V);
+    A.flip = p.nbuf == 4 ? 1 : 0;
     A.coef = ws + p.coef_at;
     A.part = reinterpret_cast<double *>(ws + p.part_at);
     A.onsite = f32 ? (const void *)op->onsite32 : (const void *)op->onsite64;
@@ -203,12 +201,11 @@ static int run_pipe_t(const cbdg_op *op, const PipePlan &p, const int32_t *sites
     A.n_pass = 1;
     for (int i = 0; i < passes; ++i) {
         A.n0 = 2 + i * p.L;
+        A.cur = i & 1;
         int rc = launch_pipe(A, f32, st);
         if (rc) return rc;
         hipLaunchKernelGGL((k_pipe_reduce<T>), dim3((unsigned)ceil_div((int64_t)p.L * Bt, kBlock)), dim3(kBlock), 0, st, A, p.L);
         CBDG_CHECK_LAUNCH("k_pipe_reduce");
-        std::swap(A.x, A.xo);
-        std::swap(A.y, A.yo);
     }
     return CBDG_OK;
 }

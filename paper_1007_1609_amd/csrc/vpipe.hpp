@@ -146,15 +146,54 @@ struct PipeJob {
     int n, e0, R, P, y0, y1;
 };
 
-__device__ __forceinline__ int row_dist(int v, int yi, int Ly, int bcy)
+// The lattice row of virtual row v (periodic y: modulo Ly).
+__device__ __forceinline__ int lattice_row(int v, int Ly, bool bcy)
 {
-    int d = v - yi;
-    if (bcy) {
-        d %= Ly;
-        if (d < 0) d += Ly;
-        return min(d, Ly - d);
+    if (bcy && (unsigned)v >= (unsigned)Ly) {
+        v %= Ly;
+        if (v < 0) v += Ly;
     }
-    return d < 0 ? -d : d;
+    return v;
+}
+
+// Lattice distance in y of lattice rows ph and yi.
+__device__ __forceinline__ int row_dist(int ph, int yi, int Ly, bool bcy)
+{
+    const int d = ph < yi ? yi - ph : ph - yi;
+    return bcy ? min(d, Ly - d) : d;
+}
+
+// A pointer known to be to device memory (a generic access would make every
+// later wait of the trips wait for all loads).
+template <typename P> __device__ __forceinline__ P *as_global(P *p)
+{
+    return (P *)(__attribute__((address_space(1))) P *)p;
+}
+__device__ __forceinline__ const void *as_global(const void *p) { return as_global(reinterpret_cast<const char *>(p)); }
+
+__device__ __forceinline__ void global_pointers(PipeArgs &A)
+{
+    A.buf = as_global(A.buf);
+    A.coef = as_global(A.coef);
+    A.onsite = as_global(A.onsite);
+    A.mu_ee = as_global(A.mu_ee);
+    A.mu_he = as_global(A.mu_he);
+    A.part = as_global(A.part);
+}
+
+// The kernel's arguments, read from memory where they are used: for code that
+// runs once a pass, whose pointers would otherwise take scalar registers from
+// the trips.
+template <typename A>
+__device__ __forceinline__ A cold_args()
+{
+    using C = const __attribute__((address_space(4))) A;
+    C *q = (C *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(q));
+    A a;
+    __builtin_memcpy(&a, (const void *)q, sizeof(A));
+    global_pointers(a);
+    return a;
 }
 
 template <int K, int S, bool SEG>
@@ -219,7 +258,7 @@ __device__ __forceinline__ void pipe_seed(const PipeArgs &A, int b, int si, int 
     const int yi = si / Lx, xi = si - yi * Lx;
     const OnSite<T> o = reinterpret_cast<const OnSite<T> *>(A.onsite)[si];
     const T th = T(A.th);
-    V *v0 = reinterpret_cast<V *>(A.x) + b * A.Dv, *v1 = reinterpret_cast<V *>(A.y) + b * A.Dv;
+    V *v0 = reinterpret_cast<V *>(A.buf) + b * A.Dv, *v1 = reinterpret_cast<V *>(A.buf + A.one) + b * A.Dv;
     const int xl = xi > 0 ? xi - 1 : (A.bcx ? Lx - 1 : -1), xr = xi + 1 < Lx ? xi + 1 : (A.bcx ? 0 : -1);
     const int yd = yi > 0 ? yi - 1 : (A.bcy ? Ly - 1 : -1), yu = yi + 1 < Ly ? yi + 1 : (A.bcy ? 0 : -1);
     const int rowp = A.rowp;
@@ -323,12 +362,9 @@ void k_vpipe(PipeArgs A)
     const int Lx = A.Lx, Ly = A.Ly, nl = A.nl;
     const int si = __builtin_amdgcn_readfirstlane(A.sites[b]);
     const bool bcy = SEG && A.bcy;
-    if (A.seed) pipe_seed<T>(A, b, si, threadIdx.x, NW * kWave);
+    if (A.seed) pipe_seed<T>(cold_args<PipeArgs>(), b, si, threadIdx.x, NW * kWave);
     if (si < 0 || si >= Lx * Ly) return;
     const int yi = si / Lx, xi = si - yi * Lx;
-    const double e1 = (double)reinterpret_cast<const OnSite<T> *>(A.onsite)[si].de;
-    const double h1 = (double)reinterpret_cast<const OnSite<T> *>(A.onsite)[si].dr;
-
     for (int i = threadIdx.x; i < S * 2 * 2 * C * NQ * kWave; i += NW * kWave) (&hand[0][0][0][0][0][0])[i] = U4{0, 0, 0, 0};
     if constexpr (C > 1)
         for (int i = threadIdx.x; i < 2 * S * K * 4; i += NW * kWave) (&edge[0][0][0][0][0])[i] = zero_pair<T, false>();
@@ -338,9 +374,7 @@ void k_vpipe(PipeArgs A)
     // outside the diamond of radius R, past the buffer's range where it does
     const int gl = half * kWave + lane;
     auto offset = [&](int g, int v, int R) -> unsigned {
-        const int rr = R - row_dist(v, yi, Ly, bcy);
-        int ph = v;
-        if (bcy) { ph = v % Ly; if (ph < 0) ph += Ly; }
+        const int ph = lattice_row(v, Ly, bcy), rr = R - row_dist(ph, yi, Ly, bcy);
         const unsigned at = (unsigned)((ph * NQ * nl + g) * 16);
         bool ok = (g < nl) & (rr >= 0) & (bcy | ((unsigned)v < (unsigned)Ly));
         if constexpr (XM == kOpenFull || XM == kOpenPart) ok = ok & (g * W <= xi + rr) & (g * W + W - 1 >= xi - rr);
@@ -364,21 +398,20 @@ void k_vpipe(PipeArgs A)
     }
     const V *pc = reinterpret_cast<const V *>(A.coef);
     auto coef_row = [&](int v, U4 *c) __attribute__((always_inline)) {
-        int ph = v;
-        if (bcy) { ph = v % Ly; if (ph < 0) ph += Ly; }
-        else ph = min(max(v, 0), Ly - 1);
+        const int ph = bcy ? lattice_row(v, Ly, true) : min(max(v, 0), Ly - 1);
         const U4 *q = reinterpret_cast<const U4 *>(pc) + (int64_t)ph * NQ * nl + min(gl, nl - 1);
 #pragma unroll
         for (int j = 0; j < NQ; ++j) c[j] = q[j * nl];
     };
 
-    // pass p reads pair p & flip and writes the other one (flip 0: in place)
-    const int flip = A.xo != A.x ? 1 : 0;
-    const int64_t vbytes = A.Dv * (int64_t)(2 * sizeof(T)), vbase = b * vbytes;
-    auto vec_of = [&](bool second, bool old) -> __amdgpu_buffer_rsrc_t {
-        const uint64_t p0 = reinterpret_cast<uint64_t>(old ? A.x : A.y), p1 = reinterpret_cast<uint64_t>(old ? A.xo : A.yo);
-        char *base = reinterpret_cast<char *>((second ? p1 : p0) + (uint64_t)vbase);
-        return __builtin_amdgcn_make_buffer_rsrc(base, (short)0, (int)vbytes, kRsrcWord3);
+    // Pass p reads pair (p + cur) & flip of buffers and writes the next one
+    // (flip 0: in place); a pair is a_{n-2} and a_{n-1} of the whole tile.
+    const int vbytes = (int)(A.Dv * (int64_t)(2 * sizeof(T)));
+    const uint64_t vbase = reinterpret_cast<uint64_t>(A.buf) + (uint64_t)b * (uint64_t)vbytes, one = (uint64_t)A.one;
+    const int flip = A.flip, cur = A.cur;
+    auto vec_of = [&](int pass, int newer) -> __amdgpu_buffer_rsrc_t {
+        const uint64_t at = vbase + ((pass + cur) & flip ? 2 * one : 0) + (newer ? one : 0);
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char *>(at), (short)0, vbytes, kRsrcWord3);
     };
 
     // half of the wavefronts feed a_{n-1}'s rows, the others a_{n-2}'s
@@ -389,7 +422,7 @@ void k_vpipe(PipeArgs A)
     auto feed_load = [&](U4 *d) __attribute__((always_inline)) {
         const int c = ft + 1 - fk;
         const bool in = (unsigned)c < (unsigned)F.R;
-        const auto rs = vec_of(fp & flip, fk);
+        const auto rs = vec_of(fp, 1 - fk);
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             const int j = fw + f * (NW / 2);
@@ -573,8 +606,7 @@ void k_vpipe(PipeArgs A)
             const bool l1 = (unsigned)(jt - (K - 1)) < (unsigned)J.R && s1 >= J.y0 && s1 < J.y1;
             const bool l2 = (unsigned)(jt - K) < (unsigned)J.R && s2 >= J.y0 && s2 < J.y1;
             const unsigned o1 = l1 ? offset(gl, s1, J.n + L - 1) : kOut, o2 = l2 ? offset(gl, s2, J.n + L - 2) : kOut;
-            const bool to = flip & (jp + 1);
-            const auto r1 = vec_of(to, false), r2 = vec_of(to, true);
+            const auto r1 = vec_of(jp + 1, 1), r2 = vec_of(jp + 1, 0);
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 __builtin_amdgcn_raw_buffer_store_b128(pack<T>(out + q * kPer<T>), r1, o1 + q * cstep, 0, 0);
@@ -604,12 +636,18 @@ void k_vpipe(PipeArgs A)
                         s[k] = sums[stg][0][3 * lane + k];
                         if constexpr (C > 1) s[k] += sums[stg][1][3 * lane + k];
                     }
-                    if (!SEG || A.n_segs == 1) {
-                        pipe_moments(A, (int64_t)b * A.N, done + lane, s, e1, h1);
+                    // (two halves: the registers a fresh read takes cost more,
+                    // 512x512, N = 512: 43.5 ms against 49.6)
+                    PipeArgs B;
+                    if constexpr (C > 1) B = A;
+                    else B = cold_args<PipeArgs>();
+                    if (!SEG || B.n_segs == 1) {
+                        const OnSite<T> o = reinterpret_cast<const OnSite<T> *>(B.onsite)[si];
+                        pipe_moments(B, (int64_t)b * B.N, done + lane, s, (double)o.de, (double)o.dr);
                     } else {
 #pragma unroll
                         for (int k = 0; k < 3; ++k)
-                            A.part[(((int64_t)(stg * K + lane) * A.n_segs + seg) * 3 + k) * A.Bt + b] = s[k];
+                            B.part[(((int64_t)(stg * K + lane) * B.n_segs + seg) * 3 + k) * B.Bt + b] = s[k];
                     }
                 }
                 done = 0;
