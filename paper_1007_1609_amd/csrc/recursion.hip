@@ -1587,6 +1587,12 @@ static int run_moments(const cbdg_op *op, const int32_t *sites, int64_t n_start,
                 have_records = true;
                 continue;
             }
+            if (!nb_ee && gstep_plan(op, Bt, N, f32, room)) {
+                int rc = run_gstep(op, f32, ts, Bt, N, ws, mee, mhe, st);
+                if (rc) return rc;
+                have_records = false;
+                continue;
+            }
         }
         have_records = false;
         const int64_t nz = L2 * Bp;

@@ -203,6 +203,11 @@ int run_gpipe(const cbdg_op *op, const GPipePlan &p, bool f32, const int32_t *si
 
 // The sites' records in rows of nl lanes of W columns, recs values per row.
 int launch_gpipe_records(const cbdg_op *op, int W, int nl, int recs, bool f32, void *ws, hipStream_t st);
+// One step per launch with each vector clipped to its own light cone, for the
+// same operators under doubling (gstep.hip).
+bool gstep_plan(const cbdg_op *op, int Bt, int N, bool f32, int64_t room);
+int run_gstep(const cbdg_op *op, bool f32, const int32_t *sites, int Bt, int N, void *ws, double *mu_ee, double *mu_he,
+              hipStream_t st);
 
 // a_0 (its whole start row) and the zeroth moments of a tile
 int launch_vc_seed(void *a0, int64_t Dv, int Lx, bool f32, int Bt, int64_t L2, const int32_t *sites, double *mu_ee,
