@@ -1496,8 +1496,21 @@ static int run_moments(const cbdg_op *op, const int32_t *sites, int64_t n_start,
         auto vc_reduce = [&](int segs, int n, int ns) -> int {
             return segs == 1 ? CBDG_OK : reduce(segs, n, ns, Bt, Bp, mee, mhe);
         };
-        int rc = launch_vc_seed(buf[0], L2, op->Lx, f32, Bt, L2, ts, mee, mhe, N, st);
-        if (rc) return rc;
+        const int n_steps = N / 2;
+        S *P2 = buf[0], *P1 = buf[1], *Q0 = buf[2], *Q1 = buf[3];
+        // For the reverse pass, which needs a_M and a_{M+1} themselves: whole
+        // pipelined passes first, these the steps left (128x128, N = 512, 1024
+        // vectors: 4.8 + 0.8 ms in place of 7.4).
+        int done = 0, at = 0, rc = CBDG_OK;
+        if (vc_out && !f32) {
+            void *const pb[4] = {buf[0], buf[1], buf[2], buf[3]};
+            if ((rc = run_pipe_prefix(op, ts, Bt, N, n_steps, pb, vc_coef, mee, mhe, &done, &at, st))) return rc;
+            if (at) {
+                std::swap(P2, Q0);
+                std::swap(P1, Q1);
+            }
+        }
+        if (!done && (rc = launch_vc_seed(buf[0], L2, op->Lx, f32, Bt, L2, ts, mee, mhe, N, st))) return rc;
         VcArgs V{};
         V.coef = vc_coef;
         V.th = op->t / op->bounds.a;
@@ -1507,12 +1520,10 @@ static int run_moments(const cbdg_op *op, const int32_t *sites, int64_t n_start,
         const int KS = vc_steps(f32);
         const int segs1 = (int)std::min<int64_t>(vc_segments(op->Ly, Bt, 1), Rmax);
         const int segsK = (int)std::min<int64_t>(vc_segments(op->Ly, Bt, KS), Rmax);
-        const int n_steps = N / 2;
-        S *P2 = buf[0], *P1 = buf[1], *Q0 = buf[2], *Q1 = buf[3];
         V.part = part; V.pstride = pstride;
         V.n = 1; V.a1 = P2; V.a2 = P2; V.out = P1; V.n_segs = segs1;
-        if ((rc = launch_vc(V, 1, f32, st)) || (rc = vc_reduce(segs1, 1, 1))) return rc;
-        int n = 2;
+        if (!done && ((rc = launch_vc(V, 1, f32, st)) || (rc = vc_reduce(segs1, 1, 1)))) return rc;
+        int n = std::max(done, 1) + 1;
         V.n_segs = segsK;
         for (; n + KS - 1 <= n_steps; n += KS) {
             V.n = n; V.a2 = P2; V.a1 = P1; V.out = Q0; V.out2 = Q1;

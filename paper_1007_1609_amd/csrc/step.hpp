@@ -190,6 +190,13 @@ PipePlan pipe_plan(const cbdg_op *op, int Bt, bool f32, int64_t limit);
 int run_pipe(const cbdg_op *op, const PipePlan &p, bool f32, const int32_t *sites, int Bt, int N, void *ws, double *mu_ee,
              double *mu_he, bool coef, hipStream_t st);
 
+// As many whole pipelined passes of the FP64 recursion as fit into `steps` steps
+// (seed included), on the seven-step passes' own buffers (buf[0..3], lying one
+// after the other) and coefficients: *done of the steps are taken, a_{done-1}
+// and a_done in buf[*at], buf[*at + 1].  *done = 0: these passes do not apply.
+int run_pipe_prefix(const cbdg_op *op, const int32_t *sites, int Bt, int N, int steps, void *const *buf, const void *coef,
+                    double *mu_ee, double *mu_he, int *done, int *at, hipStream_t st);
+
 // The general row pipeline (gpipe.hpp): complex and per-bond operators under
 // doubling, every operator's neighbour moments (direct).  W = 0: not for this
 // tile.  The workspace holds the records, then nbuf buffers of `grid` vectors.

@@ -164,25 +164,55 @@ __global__ void k_pipe_reduce(PipeArgs A, int L)
     pipe_moments(A, (int64_t)b * A.N, A.n0 + lev, s, (double)o.de, (double)o.dr);
 }
 
-template <typename T>
-static int run_pipe_t(const cbdg_op *op, const PipePlan &p, const int32_t *sites, int Bt, int N, char *ws, double *mu_ee,
-                      double *mu_he, bool coef, hipStream_t st)
+// The operator's part of a launch's arguments.
+static PipeArgs pipe_args(const cbdg_op *op, const PipePlan &p, bool f32, int Bt, int N, const int32_t *sites, double *mu_ee,
+                          double *mu_he)
 {
-    using V = typename Storage<T, false>::type;
-    constexpr bool f32 = sizeof(T) == 4;
     PipeArgs A{};
-    A.buf = ws;
-    A.one = p.Dv * Bt * (int64_t)sizeof(V);
     A.flip = p.nbuf == 4 ? 1 : 0;
-    A.coef = ws + p.coef_at;
-    A.part = reinterpret_cast<double *>(ws + p.part_at);
     A.onsite = f32 ? (const void *)op->onsite32 : (const void *)op->onsite64;
     A.th = op->t / op->bounds.a;
     A.lim = moment_limit(f32);
     A.Lx = op->Lx; A.Ly = op->Ly; A.bcx = op->bc_x; A.bcy = op->bc_y;
     A.W = p.W; A.nl = p.nl; A.rowp = p.rowp; A.Dv = p.Dv;
     A.Bt = Bt; A.N = N; A.n_segs = p.segs;
+    A.n0 = 2;
     A.sites = sites; A.mu_ee = mu_ee; A.mu_he = mu_he;
+    return A;
+}
+
+// Rows of 64 W columns lie as the seven-step passes keep them, so that those
+// can take the recursion over at any step.
+int run_pipe_prefix(const cbdg_op *op, const int32_t *sites, int Bt, int N, int steps, void *const *buf, const void *coef,
+                    double *mu_ee, double *mu_he, int *done, int *at, hipStream_t st)
+{
+    *done = *at = 0;
+    const PipePlan p = pipe_plan(op, Bt, false, INT64_MAX);
+    if (!p.W || p.segs != 1 || p.nl * p.W != op->Lx || p.W != vc_width(op->Lx, false)) return CBDG_OK;
+    const int passes = (steps - 1) / p.L;
+    if (passes < 1) return CBDG_OK;
+    PipeArgs A = pipe_args(op, p, false, Bt, N, sites, mu_ee, mu_he);
+    A.buf = reinterpret_cast<char *>(buf[0]);
+    A.one = reinterpret_cast<char *>(buf[1]) - A.buf;
+    A.coef = coef;
+    A.seed = 1;
+    A.n_pass = passes;
+    *done = 1 + passes * p.L;
+    *at = passes & A.flip ? 2 : 0;
+    return launch_pipe(A, false, st);
+}
+
+template <typename T>
+static int run_pipe_t(const cbdg_op *op, const PipePlan &p, const int32_t *sites, int Bt, int N, char *ws, double *mu_ee,
+                      double *mu_he, bool coef, hipStream_t st)
+{
+    using V = typename Storage<T, false>::type;
+    constexpr bool f32 = sizeof(T) == 4;
+    PipeArgs A = pipe_args(op, p, f32, Bt, N, sites, mu_ee, mu_he);
+    A.buf = ws;
+    A.one = p.Dv * Bt * (int64_t)sizeof(V);
+    A.coef = ws + p.coef_at;
+    A.part = reinterpret_cast<double *>(ws + p.part_at);
     if (coef) {
         hipLaunchKernelGGL((k_pipe_coef<T>), dim3((unsigned)std::min<int64_t>(ceil_div(p.Dv, kBlock), 4096)), dim3(kBlock),
                            0, st, reinterpret_cast<const OnSite<T> *>(A.onsite), reinterpret_cast<V *>(ws + p.coef_at),
@@ -190,7 +220,6 @@ static int run_pipe_t(const cbdg_op *op, const PipePlan &p, const int32_t *sites
         CBDG_CHECK_LAUNCH("k_pipe_coef");
     }
     const int steps = N / 2 - 1, passes = (int)ceil_div(steps, p.L);
-    A.n0 = 2;
     if (p.segs == 1 && steps > 0) {
         A.seed = 1;
         A.n_pass = passes;
