@@ -731,12 +731,19 @@ __global__ __launch_bounds__(kVcBlock) __attribute__((amdgpu_waves_per_eu(1))) v
     g.Lx = Lx; g.Ly = Ly;
     g.yi = si / Lx; g.xi = si - g.yi * Lx;
     g.lo = lane * W; g.lane = lane;
-    const int per = max(4, (Ly + A.n_segs - 1) / A.n_segs);
-    const int y0 = seg * per, y1 = min(y0 + per, Ly);
-    if (y0 >= y1) return;
     const int m0 = A.m0;
     const int nlev = VAR ? A.nlev : K;
     const bool first = A.first != 0;
+    // the rows within m0 of the start site, shared out; the first pass writes
+    // the whole of G
+    int top = 0, end = Ly;
+    if (!first && (!BCY || 2 * m0 + 1 < Ly)) {
+        top = BCY ? g.yi - m0 : max(0, g.yi - m0);
+        end = BCY ? g.yi + m0 + 1 : min(Ly, g.yi + m0 + 1);
+    }
+    const int per = max(4, (end - top + A.n_segs - 1) / A.n_segs);
+    const int y0 = top + seg * per, y1 = min(y0 + per, end);
+    if (y0 >= y1) return;
 
     // cotangent coefficients of the pass's levels (wave-uniform)
     double cA[K], cP[K], cQ[K], cR[K], cS[K], cg[K];
@@ -769,10 +776,13 @@ __global__ __launch_bounds__(kVcBlock) __attribute__((amdgpu_waves_per_eu(1))) v
     const auto rco1 = vec_rsrc<T>(A.co1, b, A.Dv), rco2 = vec_rsrc<T>(A.co2, b, A.Dv);
     const auto rg = vec_rsrc<T>(A.G, b, A.Dv);
     const T th = kCoefScale<T> * T(A.th);
-    // row offsets: the forward vectors inside their cones, the cotangents and
-    // G over every lattice row (not loaded at all on the first pass)
+    // Row offsets inside a radius: a_m vanishes outside radius m; of lam_m only
+    // radius m is kept, all that the terms lam_m . dHt a_{m-1} and the later
+    // cotangents inside their own radii depend on.  The cotangents and G are not
+    // loaded on the first pass.
     auto off_b = [&](int v, int R) -> unsigned { return g.template offset<T, W>(v, R); };
-    auto off_c = [&](int v) -> unsigned { return first ? kOut : g.template offset<T, W>(v, kFar); };
+    auto off_c = [&](int v, int R) -> unsigned { return first ? kOut : g.template offset<T, W>(v, R); };
+    const int gR = first ? kFar : m0;
     auto own = [&](int v) -> bool { return (unsigned)(v - y0) < (unsigned)(y1 - y0); };
 
     constexpr int NQ = W / kPer<T>;
@@ -805,12 +815,12 @@ __global__ __launch_bounds__(kVcBlock) __attribute__((amdgpu_waves_per_eu(1))) v
 #pragma unroll
     for (int i = 0; i < R1 - 1; ++i) {
         load_row<T, W>(rb1, off_b(r0 - 1 + i, m0), ab1[i]);
-        load_row<T, W>(rc1, off_c(r0 - 1 + i), ac1[i]);
+        load_row<T, W>(rc1, off_c(r0 - 1 + i, m0 + 1), ac1[i]);
     }
 #pragma unroll
     for (int i = 0; i < R2 - 1; ++i) {
         load_row<T, W>(rb0, off_b(r0 + i, m0 + 1), ab0[i]);
-        load_row<T, W>(rc0, off_c(r0 + i), ac0[i]);
+        load_row<T, W>(rc0, off_c(r0 + i, m0 + 2), ac0[i]);
     }
 #pragma unroll
     for (int j = 0; j < K - 1; ++j)
@@ -835,10 +845,10 @@ __global__ __launch_bounds__(kVcBlock) __attribute__((amdgpu_waves_per_eu(1))) v
         __builtin_amdgcn_sched_barrier(0);
         load_row<T, W>(rb0, off_b(r + D2, m0 + 1), bpn);
         load_row<T, W>(rb1, off_b(r + 1 + D1, m0), bw3);
-        load_row<T, W>(rc0, off_c(r + D2), cpn);
-        load_row<T, W>(rc1, off_c(r + 1 + D1), cw3);
+        load_row<T, W>(rc0, off_c(r + D2, m0 + 2), cpn);
+        load_row<T, W>(rc1, off_c(r + 1 + D1, m0 + 1), cw3);
         const int rg_row = r - (K - 1);
-        load_row<T, W>(rg, (!first && own(rg_row)) ? g.template offset<T, W>(rg_row, kFar) : kOut, gpre);
+        load_row<T, W>(rg, (!first && own(rg_row)) ? g.template offset<T, W>(rg_row, gR) : kOut, gpre);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < K; ++j) {
@@ -896,11 +906,11 @@ __global__ __launch_bounds__(kVcBlock) __attribute__((amdgpu_waves_per_eu(1))) v
                 }
                 if (!VAR && j == K - 2) {
                     store_row<T, W>(rbo1, off_b(s, m0 - j - 1), bn);
-                    store_row<T, W>(rco1, g.template offset<T, W>(s, kFar), cn);
+                    store_row<T, W>(rco1, g.template offset<T, W>(s, m0 - j), cn);
                 }
                 if (!VAR && j == K - 1) {
                     store_row<T, W>(rbo2, off_b(s, m0 - j - 1), bn);
-                    store_row<T, W>(rco2, g.template offset<T, W>(s, kFar), cn);
+                    store_row<T, W>(rco2, g.template offset<T, W>(s, m0 - j), cn);
                 }
             }
             if (j < K - 1) {
@@ -916,7 +926,7 @@ __global__ __launch_bounds__(kVcBlock) __attribute__((amdgpu_waves_per_eu(1))) v
         if (own(rg_row)) {
 #pragma unroll
             for (int k = 0; k < W; ++k) { gpre[k].e = gpre[k].e + ga[k].e; gpre[k].h = gpre[k].h + ga[k].h; }
-            store_row<T, W>(rg, g.template offset<T, W>(rg_row, kFar), gpre);
+            store_row<T, W>(rg, g.template offset<T, W>(rg_row, gR), gpre);
         }
 #pragma unroll
         for (int k = 0; k < W; ++k) ga[k] = zero_pair<T, false>();
