@@ -52,7 +52,58 @@ __global__ void k_gpipe_records(const OnSite<T> *__restrict__ ons, const void *_
     }
 }
 
-GPipePlan gpipe_plan(const cbdg_op *op, int Bt, bool f32, bool direct, int64_t room)
+// Steps of a pass.
+static int gpipe_steps(int W, bool f32, bool cp, bool gen)
+{
+    auto shape = [&](auto t, auto c, auto g) -> int {
+        using T = decltype(t);
+        constexpr bool CP = decltype(c)::value, GEN = decltype(g)::value;
+        switch (W) {
+        case 1: return GPipeShape<T, CP, GEN, 1>::K * GPipeShape<T, CP, GEN, 1>::S;
+        case 2: return GPipeShape<T, CP, GEN, 2>::K * GPipeShape<T, CP, GEN, 2>::S;
+        default: return GPipeShape<T, CP, GEN, 3>::K * GPipeShape<T, CP, GEN, 3>::S;
+        }
+    };
+    using yes = std::true_type;
+    using no = std::false_type;
+    return f32 ? (cp ? (gen ? shape(0.f, yes{}, yes{}) : shape(0.f, yes{}, no{}))
+                     : (gen ? shape(0.f, no{}, yes{}) : shape(0.f, no{}, no{})))
+               : (cp ? (gen ? shape(0., yes{}, yes{}) : shape(0., yes{}, no{}))
+                     : (gen ? shape(0., no{}, yes{}) : shape(0., no{}, no{})));
+}
+
+// Whether the pipeline is the faster way, by the time of either (us).  Here:
+// trips of a workgroup's vectors, 1.1 us each, more where rows wrap and with two
+// workgroups on a CU.  The one-step kernels: per step a launch (under doubling
+// with its reductions; nearly all latency on small tiles) and the tile's bytes.
+// Over 490 calls of 3 to 192 columns, 3 to 200 rows, 1 to 1024 vectors and N = 24
+// to 260 the middle 80 % of the times lie within 30 % of these.  It is the
+// neighbour moments of periodic-y lattices that stay: the workspace holds two
+// buffers a vector, the pipeline needs four of every workgroup's, and half of the
+// tile has to wait (FP64, N = 260: 11x200, 100 vectors 2.4 ms there, 11.6 here;
+// 34x80, N = 64, 1024 vectors 0.96 / 3.5; under doubling it is faster in 19 of 20
+// calls, 2.1 times on average).
+static bool gpipe_pays(const cbdg_op *op, const GPipePlan &p, int Bt, int N, bool f32, bool direct)
+{
+    const bool cp = op->scalar == CBDG_COMPLEX, gen = op->general;
+    const int L = gpipe_steps(p.W, f32, cp, gen), M = direct ? N - 1 : N / 2;
+    int64_t trips = 0;
+    for (int n = 2; n <= M; n += L) {
+        const int64_t cone = 2 * (int64_t)(n + L - 1) + 1;
+        const int64_t rows = cone < op->Ly ? cone : op->Ly + (op->bc_y ? 2 * L : 0);
+        trips += std::max<int64_t>(rows + L / 4 + 8, L + 12);
+    }
+    const double trip = (direct ? 1.15 : 1.1) * (op->bc_x || op->bc_y ? (direct ? 1.45 : 1.25) : 1.0) * (p.grid > 256 ? 1.35 : 1.0);
+    const double here = 25.0 + (double)(trips * ceil_div(Bt, p.grid)) * trip;
+    const int kind = gen ? (cp ? 2 : 1) : 0;
+    static const double kLaunch[2][3] = {{14, 15, 16}, {8, 12, 13}};  // us a step
+    static const double kRate[3] = {2.2e6, 1.9e6, 1.6e6};             // bytes of one vector a us
+    const double launch = kLaunch[direct][kind] * (op->Ly < 8 ? 0.75 : 1.0);
+    const double bytes = (double)op->L2 * (double)lane_stride(Bt) * (cp ? 4 : 2) * (f32 ? 4 : 8);
+    return here <= 0.9 * (20.0 + M * (launch + bytes / kRate[kind]));
+}
+
+GPipePlan gpipe_plan(const cbdg_op *op, int Bt, int N, bool f32, bool direct, int64_t room)
 {
     GPipePlan p{};
     const bool cp = op->scalar == CBDG_COMPLEX;
@@ -78,6 +129,7 @@ GPipePlan gpipe_plan(const cbdg_op *op, int Bt, bool f32, bool direct, int64_t r
     p.buf_at = recs;
     p.nbuf = nbuf;
     p.W = W;
+    if (!gpipe_pays(op, p, Bt, N, f32, direct)) p.W = 0;
     return p;
 }
 
@@ -127,22 +179,7 @@ int run_gpipe(const cbdg_op *op, const GPipePlan &p, bool f32, const int32_t *si
     A.sites = sites; A.mu_ee = mu_ee; A.mu_he = mu_he;
     G.recs = p.recs; G.nb_ee = nb_ee; G.nb_he = nb_he;
     const int steps = nb_ee ? N - 2 : N / 2 - 1;
-    auto shape = [&](auto t, auto c, auto g) -> int {
-        using T = decltype(t);
-        constexpr bool CP = decltype(c)::value, GEN = decltype(g)::value;
-        switch (p.W) {
-        case 1: return GPipeShape<T, CP, GEN, 1>::K * GPipeShape<T, CP, GEN, 1>::S;
-        case 2: return GPipeShape<T, CP, GEN, 2>::K * GPipeShape<T, CP, GEN, 2>::S;
-        default: return GPipeShape<T, CP, GEN, 3>::K * GPipeShape<T, CP, GEN, 3>::S;
-        }
-    };
-    using yes = std::true_type;
-    using no = std::false_type;
-    const int L = f32 ? (cp ? (gen ? shape(0.f, yes{}, yes{}) : shape(0.f, yes{}, no{}))
-                            : (gen ? shape(0.f, no{}, yes{}) : shape(0.f, no{}, no{})))
-                      : (cp ? (gen ? shape(0., yes{}, yes{}) : shape(0., yes{}, no{}))
-                            : (gen ? shape(0., no{}, yes{}) : shape(0., no{}, no{})));
-    A.n_pass = steps > 0 ? (int)ceil_div(steps, L) : 0;
+    A.n_pass = steps > 0 ? (int)ceil_div(steps, gpipe_steps(p.W, f32, cp, gen)) : 0;
     if (f32) {
         if (cp) return gen ? launch_gpipe_f32_cg(G, p.grid, st) : launch_gpipe_f32_cu(G, p.grid, st);
         return gen ? launch_gpipe_f32_rg(G, p.grid, st) : launch_gpipe_f32_ru(G, p.grid, st);

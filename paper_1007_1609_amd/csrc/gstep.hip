@@ -343,9 +343,13 @@ bool gstep_plan(const cbdg_op *op, int Bt, int N, bool f32, int64_t room)
     if (f32 && op->general) return false;  // the one-step kernels' roundings (gpipe.hip)
     // The cones cover at most half of the lattice on average over the steps:
     // past that the vector-major kernels move as few bytes, with scalar
-    // coefficient loads.
+    // coefficient loads.  Small tiles they leave waiting for three launches a
+    // step (140x20, N = 260, 250 vectors 3.4 ms there, 1.9 here; 80x16, 600
+    // vectors 3.8 / 3.2), but not where rows fill few lanes here (7x200, 1024
+    // vectors 3.4 / 4.1).
     const double M = N / 2, L2 = (double)op->L2;
-    if (2.0 * M * M / 3.0 > 0.5 * L2) return false;
+    const double bytes = L2 * (double)lane_stride(Bt) * (cp ? 4 : 2) * (f32 ? 4 : 8);
+    if (2.0 * M * M / 3.0 > 0.5 * L2 && (op->Lx < 24 || bytes > 3e7)) return false;
     const int64_t vec = op->L2 * round_up((cp ? 4 : 2) * (f32 ? 4 : 8), 16);
     if (vec > INT32_MAX) return false;
     const int64_t per_vec = ceil_div(op->Lx, kWave) * std::max<int64_t>(1, op->Ly / kStepRows);

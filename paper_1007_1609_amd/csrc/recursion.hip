@@ -1590,7 +1590,7 @@ static int run_moments(const cbdg_op *op, const int32_t *sites, int64_t n_start,
         have_vc_coef = false;
         if (nb_ee || doubling) {
             const int64_t room = nb_ee ? 2 * L2 * Bp * (int64_t)sizeof(S) : moments_bytes(op, Bt, f32 ? CBDG_FP32_ACC64 : CBDG_FP64, true);
-            const GPipePlan gp = gpipe_plan(op, Bt, f32, nb_ee != nullptr, room);
+            const GPipePlan gp = gpipe_plan(op, Bt, N, f32, nb_ee != nullptr, room);
             if (gp.W) {
                 int rc = run_gpipe(op, gp, f32, ts, Bt, N, ws, mee, mhe, nb_ee ? nb_ee + t0 * 4 * N * he_mult : nullptr,
                                    nb_ee ? nb_he + t0 * 4 * N * he_mult : nullptr, !have_records, st);

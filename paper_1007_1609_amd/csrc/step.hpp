@@ -204,7 +204,7 @@ struct GPipePlan {
     int W, nl, recs, grid, nbuf;
     int64_t Dv, buf_at;
 };
-GPipePlan gpipe_plan(const cbdg_op *op, int Bt, bool f32, bool direct, int64_t room);
+GPipePlan gpipe_plan(const cbdg_op *op, int Bt, int N, bool f32, bool direct, int64_t room);
 int run_gpipe(const cbdg_op *op, const GPipePlan &p, bool f32, const int32_t *sites, int Bt, int N, void *ws, double *mu_ee,
               double *mu_he, double *nb_ee, double *nb_he, bool records, hipStream_t st);
 

@@ -36,3 +36,14 @@ def test_cones_and_blocks(Lx, Ly, bcx, bcy, kind):
         _check(w, N, 48, 0, 1e-12, sites)
         if not bond:
             _check(w, N, 70, 1, 2e-5, sites)
+
+
+@pytest.mark.parametrize("kind", [(True, False, 0.0), (True, True, 1.0 / 16.0), (False, True, 0.0)])
+@pytest.mark.parametrize("bcx,bcy", list(itertools.product((0, 1), (0, 1))))
+@pytest.mark.parametrize("Lx,Ly,N", [(140, 12, 150), (193, 5, 260), (130, 1, 150)])
+def test_small_tiles_past_the_cones(Lx, Ly, N, bcx, bcy, kind):
+    cplx, bond, flux = kind
+    if Ly < 3 and (bcy or flux):
+        pytest.skip("periodic y needs three rows")
+    w = W.small_random(Lx, Ly, N, seed=N, bc_x=bcx, bc_y=bcy, complex_=cplx, bond=bond, flux=flux, n_sites=40)
+    _check(w, N, 40, 0, 1e-12)
