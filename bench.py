@@ -17,15 +17,15 @@ the timed steps if it has not converged by then).
 Prints one JSON line.  `value` is moments/s (start vectors x N per second)
 with every input resident in HBM.  The moments come from moment doubling
 (N/2 recursion steps per tile) unless --algorithm direct asks for N - 1
-steps; on this lattice (256 = 64 x 4 columns) the library advances a tile
-seven steps per launch in the vector-contiguous passes, one wavefront per
-start vector, each vector clipped to its own light cone, the pass writing the
-doubling moments of its steps itself.  `roofline` reports the recursion
+steps; on this lattice the library takes a tile in one launch of the row
+pipeline, one workgroup per start vector, its wavefronts the stages of passes
+of 24 steps, each vector clipped to its own light cone, the passes writing the
+doubling moments of their steps themselves.  `roofline` reports the recursion
 launches, timed with HIP events on the launch stream around each tile (the
 tile's seed and coefficient kernels are charged to the recursion launches):
-`achieved` counts the bytes each launch must move through HBM -- its input
-and output vectors inside their light cones -- over the average launch
-duration; `effective_GBps` counts instead the bytes of the plain one-step
+`achieved` counts the bytes each launch must move through HBM -- the input
+and output vectors of its passes inside their light cones -- over the average
+launch duration; `effective_GBps` counts instead the bytes of the plain one-step
 recursion streamed over the whole lattice, which the multi-step passes and
 the light cone avoid.  `traffic` is the HBM traffic per launch from the
 rocprofv3 counters stored under profiles/ (null when they were taken on a
@@ -53,7 +53,8 @@ HBM_PEAK_GBS = 8000.0
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("stencil.hpp", "step.hpp", "recursion.hip", "vcstep.hip", "common.hpp"):
+    for f in ("stencil.hpp", "step.hpp", "rows.hpp", "recursion.hip", "vcstep.hip", "vpipe.hpp", "vpipe.hip",
+              "common.hpp"):
         with open(os.path.join(ROOT, "paper_1007_1609_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -138,23 +139,28 @@ def copy_probe(dev, nbytes=2 << 30, reps=8):
                       "avg_ms": ms, "GBps_read_plus_write": 2 * nbytes / (ms / 1e3) / 1e9}), flush=True)
 
 
-# Steps per launch of the vector-contiguous passes (FP64, FP32 recursion)
+# Steps per launch of the vector-contiguous passes (FP64, FP32 recursion), and
+# steps per pass of the row pipeline up to each lattice width
 VC_STEPS = {8: 7, 4: 7}
+PIPE_STEPS = {8: ((128, 20), (256, 24), (512, 12)), 4: ((256, 20), (512, 12))}
 
 
 def recursion_plan(real_uniform: bool, bt: int, s_bytes: int, Lx: int = 0, doubling: bool = True):
-    """(kernel name, layout, steps per launch) of the passes the library
-    issues for a tile of bt vectors.  Real operators with uniform hopping
-    under moment doubling on lattices with Lx = 64 W (FP64: W = 1, 2, 4;
-    FP32: W = 2, 4) take the vector-contiguous passes, seven steps per
-    launch; other real uniform operators the vector-major
-    passes, three steps per launch on tiles of more than 128 vectors and two
-    on smaller ones; other operators one step per launch."""
+    """(kernel name, layout, steps per launch or pass) of the passes the
+    library issues for a tile of bt vectors on an open lattice.  Real operators
+    with uniform hopping under moment doubling up to 512 columns wide take the
+    row pipeline, all its passes in one launch, but for the tile sizes at which
+    128 (FP64) or 256 (FP32) columns keep the seven-step vector-contiguous
+    passes; other real uniform operators the vector-major passes, three steps
+    per launch on tiles of more than 128 vectors and two on smaller ones; other
+    operators one step per launch."""
     t = "double" if s_bytes == 8 else "float"
-    W = Lx // 64 if Lx % 64 == 0 else 0
-    if real_uniform and doubling and W in ((1, 2, 4) if s_bytes == 8 else (2, 4)):
-        K = VC_STEPS[s_bytes]
-        return "k_vc_pass<%s> (%d recursion steps per launch, one wavefront per vector)" % (t, K), "vc", K
+    if real_uniform and doubling and Lx <= 512:
+        if (Lx == 128 and 32 < bt <= 128) if s_bytes == 8 else (Lx == 256 and 32 < bt <= 256):
+            K = VC_STEPS[s_bytes]
+            return "k_vc_pass<%s> (%d recursion steps per launch, one wavefront per vector)" % (t, K), "vc", K
+        K = next(k for cols, k in PIPE_STEPS[s_bytes] if Lx <= cols)
+        return "k_vpipe<%s> (one launch per tile, passes of %d recursion steps, one workgroup per vector)" % (t, K), "pipe", K
     if not real_uniform:
         return "k_cheb_step<%s> (one recursion step per launch)" % t, "vm", 1
     if bt >= 129:
@@ -178,8 +184,10 @@ def launch_bytes(tile_events, sites_np, tile, n_tiles, w, steps_per_tile, real_u
         name, layout, K = recursion_plan(real_uniform, bt, s_bytes, w.Lx, doubling)
         kernel = kernel or name
         ts = sites_np[lo:lo + bt]
-        if layout == "vc":
+        if layout != "vm":
             nl, moved, streamed = vc_traffic(ts, w.Lx, w.Ly, w.bc_x, w.bc_y, steps_per_tile, K)
+            if layout == "pipe":
+                nl = 1
             moved_b += moved * 2 * s_bytes
             streamed_b += streamed * 2 * s_bytes
         else:
