@@ -458,7 +458,7 @@ __global__ __launch_bounds__(S * kWave) __attribute__((amdgpu_waves_per_eu(2))) 
             const double lim = B.P.lim;
             const int64_t mrow = (int64_t)b * B.P.N;
             if (n >= B.P.N) return;
-            const int above = yi + 1 < Ly ? yi + 1 : 0;
+            const int above = yi + 1 < Ly ? yi + 1 : bcy ? 0 : -1;  // -1: no row
 #pragma unroll
             for (int k = 0; k < W; ++k) {
                 const int x = lane * W + k;

@@ -82,3 +82,21 @@ def test_tiles_and_invalid_sites():
     op, d_ee, d_he = gpu_moments(w, sites=sites, N=50, tile=700, algorithm=1)
     op.close()
     assert maxdiff(ee[~bad], d_ee[~bad]) <= 1e-12 and maxdiff(he[~bad], d_he[~bad]) <= 1e-12
+
+
+@pytest.mark.parametrize("precision,tol", [(0, 1e-12), (1, 2e-5)])
+@pytest.mark.parametrize("kind", KINDS + [(False, False, 0.0)])
+@pytest.mark.parametrize("Lx,bcx", [(8, 0), (8, 1), (33, 1), (100, 0)])
+def test_neighbour_moments_of_two_open_rows(Lx, bcx, kind, precision, tol):
+    """Two rows, open in y: the lower row has no -y neighbour, the upper no +y
+    one, and the row there is stays in its own slot (oracle)."""
+    import oracle
+    import paper_1007_1609_amd as P
+    w = _workload(Lx, 2, 32, bcx, 0, kind, 2 * Lx)
+    op = P.Operator.from_workload(w, DEV)
+    sites = torch.as_tensor(w.start_sites, device=DEV)
+    _, _, nb_ee, nb_he = (t.cpu().numpy() for t in P.chebyshev_moments_nb(op, sites, w.N, len(sites), precision))
+    a, b = op.bounds.a, op.bounds.b
+    op.close()
+    o_ee, o_he = oracle.neighbour_moments(oracle.workload_csr(w, a, b), Lx, 2, bcx, 0, w.start_sites, w.N)
+    assert maxdiff(nb_ee, o_ee) <= tol and maxdiff(nb_he, o_he) <= tol
