@@ -216,7 +216,7 @@ static int run_pipe_t(const cbdg_op *op, const PipePlan &p, const int32_t *sites
     if (coef) {
         hipLaunchKernelGGL((k_pipe_coef<T>), dim3((unsigned)std::min<int64_t>(ceil_div(p.Dv, kBlock), 4096)), dim3(kBlock),
                            0, st, reinterpret_cast<const OnSite<T> *>(A.onsite), reinterpret_cast<V *>(ws + p.coef_at),
-                           A.Lx, A.W, A.nl, A.rowp, A.Dv, T(pipe_folds(A.Lx, f32) ? 2 : 1));
+                           A.Lx, A.W, A.nl, A.rowp, A.Dv, T(pipe_folds(A.Lx, A.W, f32) ? 2 : 1));
         CBDG_CHECK_LAUNCH("k_pipe_coef");
     }
     const int steps = N / 2 - 1, passes = (int)ceil_div(steps, p.L);

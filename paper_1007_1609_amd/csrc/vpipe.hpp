@@ -685,9 +685,13 @@ void k_vpipe(PipeArgs A)
 }
 
 // Whether the recursion runs with doubled coefficients (2 de, 2 Delta/a,
-// 2 t/a), one operation per component less.  Rounding differs between the two
-// forms, which FP32 vectors show at the seventh digit: each lattice keeps one.
-inline bool pipe_folds(int Lx, bool f32) { return !f32 || Lx == 2 * kWave || Lx == 4 * kWave; }
+// 2 t/a), one operation per component less, as the passes of vcstep.hip do on
+// their widths.  Its sums begin with a_{n-2}, whose magnitude every rounding of
+// the chain then has; elsewhere a_{n-2} comes off last, as in the one-step
+// kernels (FP64, rms error against 80-bit vectors, folded / not: 16x16, N =
+// 2000, 1.7e-16 / 1.3e-16; 150x40, N = 512, 1.2e-16 / 0.9e-16), and FP32
+// vectors keep the bits they have there.
+inline bool pipe_folds(int Lx, int W, bool f32) { return W > 0 && W == vc_width(Lx, f32); }
 
 template <typename T, int W, int C, int XM>
 static int launch_pipe_x(const PipeArgs &A, hipStream_t st)
@@ -703,12 +707,10 @@ static int launch_pipe_x(const PipeArgs &A, hipStream_t st)
         else
             hipLaunchKernelGGL((k_vpipe<T, W, C, Sh::K, Sh::S, XM, false, FOLD>), g, bl, 0, st, A);
     };
-    // FP64 folds the factor 2 of eq. (ref2) into the coefficients everywhere,
-    // FP32 where rows are 128 or 256 wide (pipe_folds).
-    if constexpr (sizeof(T) == 8) {
-        go(std::true_type{});
-    } else if constexpr (XM == kRotate || XM == kOpenFull) {
-        if (pipe_folds(A.Lx, true)) go(std::true_type{});
+    // pipe_folds: only rows of 64 W columns, and of those the widths vc_width has
+    constexpr bool can_fold = C == 1 && (XM == kRotate || XM == kOpenFull) && (W == 2 || W == 4 || (W == 1 && sizeof(T) == 8));
+    if constexpr (can_fold) {
+        if (pipe_folds(A.Lx, W, sizeof(T) == 4)) go(std::true_type{});
         else go(std::false_type{});
     } else {
         go(std::false_type{});
