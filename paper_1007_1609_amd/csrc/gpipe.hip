@@ -47,7 +47,7 @@ __global__ void k_gpipe_records(const OnSite<T> *__restrict__ ons, const void *_
         }
         for (int k = 0; k < REC; ++k) {
             const int e = x % W * REC + k;
-            out[(int64_t)y * recs + ((int64_t)(e / per) * nl + x / W) * per + e % per] = kRecScale<T> * r[k];
+            out[(int64_t)y * recs + ((int64_t)(e / per) * nl + x / W) * per + e % per] = kRecScale<T, GEN> * r[k];
         }
     }
 }

@@ -100,59 +100,48 @@ __device__ __forceinline__ int step_site_index(int x, int y, int d, int Lx, int 
     return x + Lx * y;
 }
 
-// FP64 records hold twice the coefficients (exact), so that 2 Ht c - p of a
-// component is one chain of fused multiply-adds from -p: 74 operations a site
-// for per-bond complex operators; 106 in the one-step kernels' form, which FP32
-// keeps (its vectors would differ in the seventh digit).
-template <typename T> constexpr T kRecScale = sizeof(T) == 8 ? T(2) : T(1);
+// FP64 records of per-bond operators hold twice the coefficients (exact), so
+// that the chains below add up to 2 Ht c: 96 operations a site for complex
+// operators, a_{n-2} taken off included, 106 in the one-step kernels' form,
+// which FP32 keeps (its vectors would differ in the seventh digit).  Uniform
+// operators take apply_uniform in both types.
+template <typename T, bool GEN> constexpr T kRecScale = GEN && sizeof(T) == 8 ? T(2) : T(1);
 
-// 2 Ht c - p from a doubled record (FP64)
-template <bool CP, bool GEN>
-__device__ __forceinline__ Pair<double, CP> folded_site(const double *r, double th2, const Pair<double, CP> &c,
-                                                       const Pair<double, CP> *nb, const Pair<double, CP> &p)
+// 2 Ht c - p from a doubled per-bond record (FP64).  Every rounding of a sum has
+// its magnitude: a neighbour's terms make a chain of their own, and p comes off
+// last (rms error of neighbour moments against 80-bit vectors, 48x40, N = 256:
+// 1.9e-17 so and in the one-step kernels, 2.3e-17 with one chain through all
+// neighbours, 78 operations, 4.5e-17 with that chain begun with -p).
+template <bool CP>
+__device__ __forceinline__ Pair<double, CP> bond_site_f64(const double *r, const Pair<double, CP> &c,
+                                                          const Pair<double, CP> *nb, const Pair<double, CP> &p)
 {
 #pragma clang fp contract(off)
-    Pair<double, CP> y;
     if constexpr (CP) {
-        double er = fma_t(r[0], c.er, -p.er), ei = fma_t(r[0], c.ei, -p.ei);
-        double hr = fma_t(r[1], c.hr, -p.hr), hi = fma_t(r[1], c.hi, -p.hi);
-        er = fma_t(r[2], c.hr, fma_t(-r[3], c.hi, er));
-        ei = fma_t(r[2], c.hi, fma_t(r[3], c.hr, ei));
-        hr = fma_t(r[2], c.er, fma_t(r[3], c.ei, hr));
-        hi = fma_t(r[2], c.ei, fma_t(-r[3], c.er, hi));
-        if constexpr (GEN) {
+        double er = fma_t(r[0], c.er, fma_t(r[2], c.hr, -(r[3] * c.hi)));
+        double ei = fma_t(r[0], c.ei, fma_t(r[2], c.hi, r[3] * c.hr));
+        double hr = fma_t(r[1], c.hr, fma_t(r[2], c.er, r[3] * c.ei));
+        double hi = fma_t(r[1], c.hi, fma_t(r[2], c.ei, -(r[3] * c.er)));
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const Pair<double, true> &a = nb[q];
-                const double tr = r[4 + 4 * q], ti = r[5 + 4 * q], dr = r[6 + 4 * q], di = r[7 + 4 * q];
-                er = fma_t(-tr, a.er, fma_t(ti, a.ei, fma_t(dr, a.hr, fma_t(-di, a.hi, er))));
-                ei = fma_t(-tr, a.ei, fma_t(-ti, a.er, fma_t(dr, a.hi, fma_t(di, a.hr, ei))));
-                hr = fma_t(dr, a.er, fma_t(di, a.ei, fma_t(tr, a.hr, fma_t(ti, a.hi, hr))));
-                hi = fma_t(dr, a.ei, fma_t(-di, a.er, fma_t(tr, a.hi, fma_t(-ti, a.hr, hi))));
-            }
-        } else {
-            er = fma_t(-th2, (nb[0].er + nb[1].er) + (nb[2].er + nb[3].er), er);
-            ei = fma_t(-th2, (nb[0].ei + nb[1].ei) + (nb[2].ei + nb[3].ei), ei);
-            hr = fma_t(th2, (nb[0].hr + nb[1].hr) + (nb[2].hr + nb[3].hr), hr);
-            hi = fma_t(th2, (nb[0].hi + nb[1].hi) + (nb[2].hi + nb[3].hi), hi);
+        for (int q = 0; q < 4; ++q) {
+            const Pair<double, true> &a = nb[q];
+            const double tr = r[4 + 4 * q], ti = r[5 + 4 * q], dr = r[6 + 4 * q], di = r[7 + 4 * q];
+            er += fma_t(-tr, a.er, fma_t(ti, a.ei, fma_t(dr, a.hr, -(di * a.hi))));
+            ei += fma_t(-tr, a.ei, fma_t(-ti, a.er, fma_t(dr, a.hi, di * a.hr)));
+            hr += fma_t(dr, a.er, fma_t(di, a.ei, fma_t(tr, a.hr, ti * a.hi)));
+            hi += fma_t(dr, a.ei, fma_t(-di, a.er, fma_t(tr, a.hi, -(ti * a.hr))));
         }
-        y = Pair<double, true>{er, ei, hr, hi};
+        return Pair<double, true>{er - p.er, ei - p.ei, hr - p.hr, hi - p.hi};
     } else {
-        double e = fma_t(r[0], c.e, fma_t(r[2], c.h, -p.e)), h = fma_t(r[1], c.h, fma_t(r[2], c.e, -p.h));
-        if constexpr (GEN) {
+        double e = fma_t(r[0], c.e, r[2] * c.h), h = fma_t(r[2], c.e, r[1] * c.h);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const double t = r[4 + 2 * q], dl = r[5 + 2 * q];
-                e = fma_t(-t, nb[q].e, fma_t(dl, nb[q].h, e));
-                h = fma_t(dl, nb[q].e, fma_t(t, nb[q].h, h));
-            }
-        } else {
-            e = fma_t(-th2, (nb[0].e + nb[1].e) + (nb[2].e + nb[3].e), e);
-            h = fma_t(th2, (nb[0].h + nb[1].h) + (nb[2].h + nb[3].h), h);
+        for (int q = 0; q < 4; ++q) {
+            const double t = r[4 + 2 * q], dl = r[5 + 2 * q];
+            e += fma_t(dl, nb[q].h, -t * nb[q].e);
+            h += fma_t(dl, nb[q].e, t * nb[q].h);
         }
-        y = Pair<double, false>{e, h};
+        return Pair<double, false>{e - p.e, h - p.h};
     }
-    return y;
 }
 
 // Ht c at one site of a per-bond operator in FP32, with the roundings of the
@@ -294,7 +283,7 @@ __global__ __launch_bounds__(S * kWave) __attribute__((amdgpu_waves_per_eu(2))) 
         auto rec_at = [&](int x, int y, int i) -> T {
             const int e = x % W * REC + i;
             constexpr int per = 16 / (int)sizeof(T);
-            return recs[(int64_t)y * G.recs + ((int64_t)(e / per) * nl + x / W) * per + e % per] * (T(1) / kRecScale<T>);
+            return recs[(int64_t)y * G.recs + ((int64_t)(e / per) * nl + x / W) * per + e % per] * (T(1) / kRecScale<T, GEN>);
         };
         // a_0, a_1 and the moments that need no recursion
         __syncthreads();  // the last vector's rows are read no more
@@ -524,11 +513,11 @@ __global__ __launch_bounds__(S * kWave) __attribute__((amdgpu_waves_per_eu(2))) 
                         Q hi = k < W - 1 ? pair_at<T, CP>(cc, k < W - 1 ? k + 1 : 0) : hr;
                         if (bcx) hi = select_pair<T, CP>(lane == lr && k == kr, first, hi);
                         const Q dn = pair_at<T, CP>(dd, k), up = pair_at<T, CP>(uu, k);
-                        const T ths = lane * W + k < Lx ? kRecScale<T> * th : T(0);
+                        const T ths = lane * W + k < Lx ? th : T(0);
                         const Q nb[4] = {hi, lo, up, dn};
                         Q y;
-                        if constexpr (sizeof(T) == 8) {
-                            put_pair<T, CP>(v, k, folded_site<CP, GEN>(o4, ths, c, nb, pair_at<T, CP>(pp, k)));
+                        if constexpr (GEN && sizeof(T) == 8) {
+                            put_pair<T, CP>(v, k, bond_site_f64<CP>(o4, c, nb, pair_at<T, CP>(pp, k)));
                             continue;
                         } else if constexpr (GEN) {
                             y = bond_site_f32<CP>(o4, c, nb);

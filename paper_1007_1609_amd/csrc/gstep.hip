@@ -96,14 +96,11 @@ template <typename T, bool CP, bool GEN> struct SiteCoef {
     __device__ __forceinline__ Pair<T, CP> advance(T th, const Pair<T, CP> &c, const Pair<T, CP> &l, const Pair<T, CP> &rt,
                                                    const Pair<T, CP> &d, const Pair<T, CP> &u, const Pair<T, CP> &p) const
     {
-        if constexpr (sizeof(T) == 8) {
-            // a_{n-2} comes off last: rounding errors half of those of sums begun with it
+        if constexpr (GEN) {
+            static_assert(sizeof(T) == 8, "per-bond FP32 operators keep the one-step kernels");
             const Pair<T, CP> nb[4] = {rt, l, u, d};
-            const Pair<T, CP> h = folded_site<CP, GEN>(r, T(2) * th, c, nb, zero_pair<T, CP>());
-            if constexpr (CP) return Pair<T, CP>{h.er - p.er, h.ei - p.ei, h.hr - p.hr, h.hi - p.hi};
-            else return Pair<T, CP>{h.e - p.e, h.h - p.h};
+            return bond_site_f64<CP>(r, c, nb, p);
         } else {
-            static_assert(!GEN, "per-bond FP32 operators keep the one-step kernels");
             return cheb_combine<T, CP>(apply_uniform<T, CP>(OnSite<T>{r[0], r[1], r[2], r[3]}, th, c, l, rt, d, u), p, false);
         }
     }
