@@ -178,10 +178,11 @@ struct PipeArgs {
 };
 
 // Shape of the pipelined recursion for a tile of Bt vectors (W = 0: not for
-// this operator) and its workspace: nbuf buffers of Bt vectors, the packed
-// coefficients at byte coef_at, the segments' sums at part_at.
+// this operator; shape: its entry among those that are built) and its
+// workspace: nbuf buffers of Bt vectors, the packed coefficients at byte
+// coef_at, the segments' sums at part_at.
 struct PipePlan {
-    int W, nl, rowp, L, segs, nbuf;
+    int W, shape, nl, rowp, L, segs, nbuf;
     int64_t Dv, coef_at, part_at, bytes;
 };
 // limit: bytes of workspace it may take.

@@ -44,26 +44,26 @@ static const PipeWidth kWidths32[] = {
     pipe_width<float, 4, 2>(launch_pipe_f32_42),
 };
 
-template <typename F>
-static const PipeWidth *find_width(bool f32, F &&fits)
+static const PipeWidth *widths(bool f32, int *n)
 {
-    const PipeWidth *w = f32 ? kWidths32 : kWidths64;
-    const int n = f32 ? (int)(sizeof(kWidths32) / sizeof(*w)) : (int)(sizeof(kWidths64) / sizeof(*w));
-    for (int i = 0; i < n; ++i)
-        if (fits(w[i])) return &w[i];
-    return nullptr;
+    *n = f32 ? (int)(sizeof(kWidths32) / sizeof(*kWidths32)) : (int)(sizeof(kWidths64) / sizeof(*kWidths64));
+    return f32 ? kWidths32 : kWidths64;
 }
 
-static int launch_pipe(const PipeArgs &A, bool f32, hipStream_t st)
+// The shape that was planned: steps of a pass and sums are sized for it.
+static int launch_pipe(const PipePlan &p, const PipeArgs &A, bool f32, hipStream_t st)
 {
-    const PipeWidth *w = find_width(f32, [&](const PipeWidth &v) { return v.W == A.W && kWave * v.W * v.C >= A.Lx; });
-    if (!w) return fail(CBDG_EUNSUPPORTED, "pipelined recursion: no width for Lx = %d", A.Lx);
-    return w->launch(A, st);
+    int n;
+    const PipeWidth *w = widths(f32, &n);
+    if (p.shape < 0 || p.shape >= n || w[p.shape].W != A.W || w[p.shape].L != p.L)
+        return fail(CBDG_EUNSUPPORTED, "pipelined recursion: no shape for Lx = %d", A.Lx);
+    return w[p.shape].launch(A, st);
 }
 
 static bool plan_width(const cbdg_op *op, const PipeWidth &w, int Bt, bool f32, bool cut, int64_t limit, PipePlan &p)
 {
-    if (kWave * w.W * w.C < op->Lx) return false;
+    // the row's end lies in its last wavefront (wrapping rows close there)
+    if (kWave * w.W * w.C < op->Lx || kWave * w.W * (w.C - 1) >= op->Lx) return false;
     p = PipePlan{};
     p.W = w.W;
     p.L = w.L;
@@ -116,10 +116,15 @@ PipePlan pipe_plan(const cbdg_op *op, int Bt, bool f32, int64_t limit)
     // sites a lane): the vector-major passes keep the periodic ones (24x128,
     // 1024 vectors, N = 256: 4317 us against 7066).
     if (f32 && op->bc_y && op->Lx <= 40) return p;
-    const PipeWidth *w = nullptr;
-    for (int cut = 1; cut >= 0 && !w; --cut)
-        w = find_width(f32, [&](const PipeWidth &v) { return plan_width(op, v, Bt, f32, cut != 0, limit, p); });
-    if (!w) p.W = 0;
+    int n;
+    const PipeWidth *w = widths(f32, &n);
+    for (int cut = 1; cut >= 0; --cut)
+        for (int i = 0; i < n; ++i)
+            if (plan_width(op, w[i], Bt, f32, cut != 0, limit, p)) {
+                p.shape = i;
+                return p;
+            }
+    p.W = 0;
     return p;
 }
 
@@ -199,7 +204,7 @@ int run_pipe_prefix(const cbdg_op *op, const int32_t *sites, int Bt, int N, int 
     A.n_pass = passes;
     *done = 1 + passes * p.L;
     *at = passes & A.flip ? 2 : 0;
-    return launch_pipe(A, false, st);
+    return launch_pipe(p, A, false, st);
 }
 
 template <typename T>
@@ -223,7 +228,7 @@ static int run_pipe_t(const cbdg_op *op, const PipePlan &p, const int32_t *sites
     if (p.segs == 1 && steps > 0) {
         A.seed = 1;
         A.n_pass = passes;
-        return launch_pipe(A, f32, st);
+        return launch_pipe(p, A, f32, st);
     }
     hipLaunchKernelGGL((k_pipe_seed<T>), dim3(Bt), dim3(kBlock), 0, st, A);
     CBDG_CHECK_LAUNCH("k_pipe_seed");
@@ -231,7 +236,7 @@ static int run_pipe_t(const cbdg_op *op, const PipePlan &p, const int32_t *sites
     for (int i = 0; i < passes; ++i) {
         A.n0 = 2 + i * p.L;
         A.cur = i & 1;
-        int rc = launch_pipe(A, f32, st);
+        int rc = launch_pipe(p, A, f32, st);
         if (rc) return rc;
         hipLaunchKernelGGL((k_pipe_reduce<T>), dim3((unsigned)ceil_div((int64_t)p.L * Bt, kBlock)), dim3(kBlock), 0, st, A, p.L);
         CBDG_CHECK_LAUNCH("k_pipe_reduce");

@@ -1,0 +1,55 @@
+"""Host side of the row pipelines without a GPU: the shape that is launched is
+the planned one, whatever workspace the plan was given."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_1007_1609_amd")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    if not (os.path.exists(HIPCC) or shutil.which("hipcc")):
+        pytest.skip("no hipcc")
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_host")
+    cmd = [HIPCC, "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-w", "-I", os.path.join(ROOT, "include"),
+           "-I", os.path.join(PKG, "csrc"), os.path.join(ROOT, "tests", "native", "plan_host.cpp"), "-o", exe, "-L", PKG,
+           "-lcbdg", "-Wl,-rpath," + PKG]
+    subprocess.run(cmd, check=True)
+
+    def run(lines):
+        r = subprocess.run([exe], input="\n".join(lines), capture_output=True, text=True, check=True)
+        return r.stdout.split("\n")[:len(lines)]
+
+    return run
+
+
+def _launched(ask, calls):
+    return [None if s == "none" else tuple(int(v) for v in s.split()) for s in ask(["launch %d %d %d %d %d %d %d" % c for c in calls])]
+
+
+@pytest.mark.parametrize("f32", [0, 1])
+def test_the_planned_shape_is_launched(ask, f32):
+    """Steps of a pass by shape: 20 where a row takes up to 8 registers (two
+    wavefronts a row: 12), 24 on wider rows.  Limits from what the widest plan
+    takes downwards, so that every shape that a plan can fall back to comes up."""
+    calls = [(Lx, Ly, bcx, bcy, Bt, f32) for Lx in (64, 65, 128, 129, 192, 193, 256, 300, 384, 385, 512) for bcx in (0, 1)
+             for bcy in (0, 1) for Ly in (40, 300, 1000) for Bt in (1, 8, 64)]
+    full = _launched(ask, [c + (1 << 50,) for c in calls])
+    calls = [c + (int(p[5] * k) - d,) for c, p in zip(calls, full) if p
+             for k, d in ((1, 0), (1, 1), (0.99999, 0), (0.9999, 0), (0.999, 0), (0.99, 0), (0.9, 0), (0.6, 0))]
+    seen = set()
+    for c, plan in zip(calls, _launched(ask, calls)):
+        if plan is None:
+            continue
+        W, L, _, lW, lC, _ = plan
+        steps = 12 if lC == 2 else 20 if lW * (4 if f32 else 8) // 2 <= 8 else 24
+        assert (lW, steps) == (W, L), (c, plan)
+        # the columns of a row reach into the second wavefront
+        assert 64 * lW * (lC - 1) < c[0] <= 64 * lW * lC, (c, plan)
+        seen.add((lW, lC))
+    assert len(seen) == (4 if f32 else 6)
