@@ -139,26 +139,22 @@ def copy_probe(dev, nbytes=2 << 30, reps=8):
                       "avg_ms": ms, "GBps_read_plus_write": 2 * nbytes / (ms / 1e3) / 1e9}), flush=True)
 
 
-# Steps per launch of the vector-contiguous passes (FP64, FP32 recursion), and
-# steps per pass of the row pipeline up to each lattice width
-VC_STEPS = {8: 7, 4: 7}
+# Steps per pass of the row pipeline up to each lattice width (FP64, FP32 recursion)
 PIPE_STEPS = {8: ((128, 20), (256, 24), (512, 12)), 4: ((256, 20), (512, 12))}
 
 
 def recursion_plan(real_uniform: bool, bt: int, s_bytes: int, Lx: int = 0, doubling: bool = True):
     """(kernel name, layout, steps per launch or pass) of the passes the
-    library issues for a tile of bt vectors on an open lattice.  Real operators
-    with uniform hopping under moment doubling up to 512 columns wide take the
-    row pipeline, all its passes in one launch, but for the tile sizes at which
-    128 (FP64) or 256 (FP32) columns keep the seven-step vector-contiguous
-    passes; other real uniform operators the vector-major passes, three steps
-    per launch on tiles of more than 128 vectors and two on smaller ones; other
-    operators one step per launch."""
+    library issues for a tile of bt vectors of the benchmark's lattices (open,
+    hundreds of moments).  Real operators with uniform hopping under moment
+    doubling up to 512 columns wide take the row pipeline, all its passes in
+    one launch (the library leaves it, by the time of either, where calls are
+    short, lattices have few rows or a tile fills a part of the GPU); other real
+    uniform operators the vector-major passes, three steps per launch on tiles
+    of more than 128 vectors and two on smaller ones; other operators one step
+    per launch."""
     t = "double" if s_bytes == 8 else "float"
     if real_uniform and doubling and Lx <= 512:
-        if (Lx == 128 and 32 < bt <= 128) if s_bytes == 8 else (Lx == 256 and 32 < bt <= 256):
-            K = VC_STEPS[s_bytes]
-            return "k_vc_pass<%s> (%d recursion steps per launch, one wavefront per vector)" % (t, K), "vc", K
         K = next(k for cols, k in PIPE_STEPS[s_bytes] if Lx <= cols)
         return "k_vpipe<%s> (one launch per tile, passes of %d recursion steps, one workgroup per vector)" % (t, K), "pipe", K
     if not real_uniform:
@@ -185,9 +181,8 @@ def launch_bytes(tile_events, sites_np, tile, n_tiles, w, steps_per_tile, real_u
         kernel = kernel or name
         ts = sites_np[lo:lo + bt]
         if layout != "vm":
-            nl, moved, streamed = vc_traffic(ts, w.Lx, w.Ly, w.bc_x, w.bc_y, steps_per_tile, K)
-            if layout == "pipe":
-                nl = 1
+            _, moved, streamed = vc_traffic(ts, w.Lx, w.Ly, w.bc_x, w.bc_y, steps_per_tile, K)
+            nl = 1
             moved_b += moved * 2 * s_bytes
             streamed_b += streamed * 2 * s_bytes
         else:

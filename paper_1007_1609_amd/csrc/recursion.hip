@@ -1569,7 +1569,7 @@ static int run_moments(const cbdg_op *op, const int32_t *sites, int64_t n_start,
         if constexpr (!C) {
             if (!vc_out && !nb_ee && doubling) {
                 const int64_t room = moments_bytes(op, Bt, f32 ? CBDG_FP32_ACC64 : CBDG_FP64, true);
-                const PipePlan pp = pipe_plan(op, Bt, f32, room);
+                const PipePlan pp = pipe_plan(op, Bt, N, f32, room);
                 if (pp.W) {
                     int rc = run_pipe(op, pp, f32, ts, Bt, N, ws, mee, mhe, pipe_coef != pp.coef_at * 16 + pp.W, st);
                     if (rc) return rc;

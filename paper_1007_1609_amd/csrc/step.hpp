@@ -185,8 +185,8 @@ struct PipePlan {
     int W, shape, nl, rowp, L, segs, nbuf;
     int64_t Dv, coef_at, part_at, bytes;
 };
-// limit: bytes of workspace it may take.
-PipePlan pipe_plan(const cbdg_op *op, int Bt, bool f32, int64_t limit);
+// N: moments; limit: bytes of workspace it may take.
+PipePlan pipe_plan(const cbdg_op *op, int Bt, int N, bool f32, int64_t limit);
 // The moments of a tile; coef: the coefficients at ws + coef_at are to be written.
 int run_pipe(const cbdg_op *op, const PipePlan &p, bool f32, const int32_t *sites, int Bt, int N, void *ws, double *mu_ee,
              double *mu_he, bool coef, hipStream_t st);

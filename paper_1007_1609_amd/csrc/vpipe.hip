@@ -3,6 +3,7 @@
 #include "vpipe.hpp"
 
 #include <algorithm>
+#include <cmath>
 
 namespace cbdg {
 
@@ -18,30 +19,35 @@ int launch_pipe_f32_41(const PipeArgs &A, hipStream_t st);
 int launch_pipe_f32_42(const PipeArgs &A, hipStream_t st);
 
 // The shapes that are built: lanes of W columns, C wavefronts per row, in the
-// order of the widest row they take.
+// order of the widest row they take.  one, two: microseconds a trip takes with
+// one and with two workgroups on a CU (two: where it holds them); wrap: how much
+// longer where rows close across lanes (kWrap).
 struct PipeWidth {
-    int W, C, L, per_cu;  // columns, wavefronts per row, steps of a pass, workgroups per CU
+    int W, C, L, S, per_cu;  // columns, wavefronts per row, steps and stages of a pass, workgroups per CU
+    int lead, drain;         // trips of a pass beside its rows, of a launch until its last stage has finished
+    double one, two, wrap;
     int (*launch)(const PipeArgs &, hipStream_t);
 };
 template <typename T, int W, int C>
-static constexpr PipeWidth pipe_width(int (*launch)(const PipeArgs &, hipStream_t))
+static constexpr PipeWidth pipe_width(int (*launch)(const PipeArgs &, hipStream_t), double one, double two, double wrap)
 {
     using Sh = PipeShape<T, W, C>;
-    return PipeWidth{W, C, Sh::K * Sh::S, 4 * Sh::waves / (Sh::S * C), launch};
+    return PipeWidth{W, C, Sh::K * Sh::S, Sh::S, 4 * Sh::waves / (Sh::S * C), Sh::K + kCoefAhead<Sh::K> + kRound<Sh::K>,
+                     kPipeAhead + (Sh::S - 1) * (Sh::K + 1) + 2 * kRound<Sh::K>, one, two, wrap, launch};
 }
 static const PipeWidth kWidths64[] = {
-    pipe_width<double, 1, 1>(launch_pipe_f64_11),
-    pipe_width<double, 2, 1>(launch_pipe_f64_21),
-    pipe_width<double, 3, 1>(launch_pipe_f64_31),
-    pipe_width<double, 4, 1>(launch_pipe_f64_41),
-    pipe_width<double, 3, 2>(launch_pipe_f64_32),
-    pipe_width<double, 4, 2>(launch_pipe_f64_42),
+    pipe_width<double, 1, 1>(launch_pipe_f64_11, 0.67, 0.82, 1.5),
+    pipe_width<double, 2, 1>(launch_pipe_f64_21, 0.97, 1.28, 1.45),
+    pipe_width<double, 3, 1>(launch_pipe_f64_31, 1.33, 0.0, 1.45),
+    pipe_width<double, 4, 1>(launch_pipe_f64_41, 1.60, 0.0, 1.75),
+    pipe_width<double, 3, 2>(launch_pipe_f64_32, 1.55, 0.0, 1.3),
+    pipe_width<double, 4, 2>(launch_pipe_f64_42, 2.40, 0.0, 1.4),
 };
 static const PipeWidth kWidths32[] = {
-    pipe_width<float, 1, 1>(launch_pipe_f32_11),
-    pipe_width<float, 2, 1>(launch_pipe_f32_21),
-    pipe_width<float, 4, 1>(launch_pipe_f32_41),
-    pipe_width<float, 4, 2>(launch_pipe_f32_42),
+    pipe_width<float, 1, 1>(launch_pipe_f32_11, 0.72, 0.94, 1.3),
+    pipe_width<float, 2, 1>(launch_pipe_f32_21, 0.89, 1.10, 1.35),
+    pipe_width<float, 4, 1>(launch_pipe_f32_41, 1.53, 2.12, 1.3),
+    pipe_width<float, 4, 2>(launch_pipe_f32_42, 1.74, 0.0, 1.1),
 };
 
 static const PipeWidth *widths(bool f32, int *n)
@@ -97,31 +103,97 @@ static bool plan_width(const cbdg_op *op, const PipeWidth &w, int Bt, bool f32, 
     return p.bytes <= limit;
 }
 
-PipePlan pipe_plan(const cbdg_op *op, int Bt, bool f32, int64_t limit)
+// Whether the pipeline is the faster way, by the time of either (us), both
+// fitted to 43000 calls of 1 to 512 columns, 3 to 300 rows, 1 to 2000 vectors
+// and N = 5 to 512, open and periodic.  Nine of ten times lie within 15 % (here,
+// seven-step passes) and 35 % (vector-major passes) of these; the calls take
+// 0.6 % more time, in the geometric mean, than with the faster way each time.
+// Against the other passes alone they are 1.25 (FP64, 64, 128 and 256 columns),
+// 1.53 (FP32), 1.94 and 1.74 times faster (other widths), with the pipeline
+// alone 0.95, 1.25, 1.74 and 1.63 times.
+//
+// Here: trips.  A pass of L steps runs all of them however few are left (64x200
+// periodic, 128 vectors, us here and in the seven-step passes: N = 48 207 / 150,
+// N = 512 1597 / 1750), and on short lattices more trips than rows (256x6, N =
+// 256, 1024 vectors 1622 / 669).  Rows beside a workgroup's own take no sums.
+static double pipe_time(const cbdg_op *op, const PipePlan &p, const PipeWidth &w, int Bt, int N, bool f32)
+{
+    const int64_t Ly = op->Ly, L = w.L, slots = 256 * (int64_t)w.per_cu, nb = (int64_t)Bt * p.segs;
+    double trips = 0.0, halo = 0.0;
+    int passes = 0;
+    for (int64_t n = 2; n <= N / 2; n += L, ++passes) {
+        const int64_t cone = 2 * (n + L - 1) + 1, in = std::min(Ly, cone);
+        const bool wrap = op->bc_y && cone >= Ly;
+        const int64_t own = p.segs > 1 ? std::max<int64_t>(4, ceil_div(in, p.segs)) : in;
+        const int64_t rows = wrap ? own + 2 * L : std::min(in, own + (p.segs > 1 ? 2 * L : 0));
+        const int64_t t = std::max(rows + w.lead, L + w.S + 6);
+        trips += (double)(t + (p.segs > 1 ? w.drain : 0));
+        halo += (double)(t - own);
+    }
+    if (p.segs == 1) trips += w.drain;
+    trips -= (f32 ? 0.25 : 0.1) * halo;
+    double trip = (double)(nb / slots) * (w.per_cu == 2 ? w.two : w.one);
+    if (nb % slots) trip += w.per_cu == 2 && nb % slots > 256 ? w.two : w.one;
+    if (op->bc_x && (w.C > 1 || op->Lx != kWave * w.W)) trip *= w.wrap;
+    // (25 us in the fit: calls that are little more than launches stay there)
+    return 35.0 + trips * trip + (p.segs > 1 ? 6.0 * passes : 0.0);
+}
+
+// The seven-step passes: launches, trips of a wavefront (1024 at a time), bytes.
+static double vc_time(const cbdg_op *op, int vw, int Bt, int N, bool f32)
+{
+    // by lanes' width 1, 2, 4: us a launch, us a trip, bytes a us
+    static const double kCost[2][3][3] = {{{6.4, 0.70, 1e9}, {3.8, 1.17, 11.5e6}, {3.4, 2.13, 12.6e6}},
+                                          {{0, 0, 1e9}, {7.0, 0.88, 1e9}, {3.8, 1.57, 12.6e6}}};
+    const double *c = kCost[f32][vw == 4 ? 2 : vw - 1];
+    const int K = vc_steps(f32), M = N / 2, segs = vc_segments(op->Ly, Bt, K);
+    const int64_t rounds = ceil_div((int64_t)Bt * segs, 1024);
+    const double row = (double)op->Lx * Bt * (f32 ? 8 : 16), trip = c[1] * (op->bc_y ? 1.15 : 1.0);
+    double us = 28.0;
+    auto in = [&](int64_t m) { return (double)std::min<int64_t>(op->Ly, 2 * m + 1); };
+    for (int n = 1; n <= M;) {
+        const int left = M - n + 1, k = n == 1 ? 1 : left >= K ? K : left;
+        const double rows = std::max(std::ceil(in(n + k - 1) / segs), 4.0) + 2.0 * (k - 1);
+        us += c[0] + (segs > 1 ? 9.0 : 0.0) +
+              std::hypot((double)rounds * rows * (k > 1 ? trip : 0.3 * c[1]), (2.0 * in(n) + 2.0 * in(n + k - 1)) * row / c[2]);
+        n += k;
+    }
+    return us;
+}
+
+// The vector-major passes of three or two steps: launches and bytes, more of
+// them where strips are narrow; the tile's start sites taken to lie in a run.
+static double vm_time(const cbdg_op *op, int Bt, int N, bool f32)
+{
+    static const double kCost[2][4] = {{18.1, 4.7, 0.48, 3.3e6}, {20.7, 0.9, 1.38, 3.6e6}};
+    const double *c = kCost[f32];
+    const int k3 = Bt > 128 ? 3 : 2, M = N / 2;
+    const int strip = k3 == 2 && op->Lx % 8 == 0 ? 8 : op->Lx % 4 == 0 ? 4 : op->Lx % 2 == 0 ? 2 : 1;
+    const double row = (double)op->Lx * (double)lane_stride(Bt) * (f32 ? 8 : 16);
+    double us = 30.0 + 3.0 * op->Ly * row / 20e6;
+    for (int n = 1; n <= M;) {
+        const int left = M - n + 1, k = n == 1 ? 1 : std::min(k3, left);
+        const int64_t cone = ceil_div(Bt, op->Lx) + 2 * (int64_t)(n + k - 1);
+        const double rows = n == 1 || op->bc_y ? op->Ly : (double)std::min<int64_t>(op->Ly, cone);
+        us += c[0] + c[1] * (k - 1) + (n == 1 ? 2.0 : k > 1 ? 4.0 : 3.0) * rows * row * (1.0 + (k > 1 ? c[2] / strip : 0.0)) / c[3];
+        n += k;
+    }
+    return us;
+}
+
+PipePlan pipe_plan(const cbdg_op *op, int Bt, int N, bool f32, int64_t limit)
 {
     PipePlan p{};
     if (op->scalar != CBDG_REAL || op->general || op->bounds.b != 0.0) return p;
-    // Where the seven-step passes apply too they keep two ranges.  A short
-    // periodic lattice is run through L rows more at either end on every pass
-    // here, through six there (1024 vectors, N = 256, us: 256x24 2017 there,
-    // 3179 here; 128x24 2249 / 2721; 128x64 2164 / 2234, 256x128 6600 / 6551).
-    // A quarter to a half of the workgroups a launch can hold: there row
-    // segments fill the GPU at less recomputation (N = 256, us: 128x256, 128
-    // vectors 1022 / 1132, 32 vectors 1010 / 810; FP32 256x256, 64 vectors 953
-    // / 1231, 256 vectors 1856 / 2026, 512 vectors 3560 / 2870).
-    const int vw = vc_width(op->Lx, f32);
-    if (vw > 0 && op->bc_y && op->Ly <= 16 * (vw + 1)) return p;
-    if (vw == (f32 ? 4 : 2) && Bt > 32 && Bt <= (f32 ? 256 : 128)) return p;
-    // FP32 rows of up to 40 sites fill a third of a wavefront or less here (two
-    // sites a lane): the vector-major passes keep the periodic ones (24x128,
-    // 1024 vectors, N = 256: 4317 us against 7066).
-    if (f32 && op->bc_y && op->Lx <= 40) return p;
     int n;
     const PipeWidth *w = widths(f32, &n);
     for (int cut = 1; cut >= 0; --cut)
         for (int i = 0; i < n; ++i)
             if (plan_width(op, w[i], Bt, f32, cut != 0, limit, p)) {
+                const int vw = vc_width(op->Lx, f32);
+                const double there = vw ? vc_time(op, vw, Bt, N, f32) : vm_time(op, Bt, N, f32);
                 p.shape = i;
+                if (pipe_time(op, p, w[i], Bt, N, f32) > there) p.W = 0;
                 return p;
             }
     p.W = 0;
@@ -192,7 +264,7 @@ int run_pipe_prefix(const cbdg_op *op, const int32_t *sites, int Bt, int N, int 
                     double *mu_ee, double *mu_he, int *done, int *at, hipStream_t st)
 {
     *done = *at = 0;
-    const PipePlan p = pipe_plan(op, Bt, false, INT64_MAX);
+    const PipePlan p = pipe_plan(op, Bt, N, false, INT64_MAX);
     if (!p.W || p.segs != 1 || p.nl * p.W != op->Lx || p.W != vc_width(op->Lx, false)) return CBDG_OK;
     const int passes = (steps - 1) / p.L;
     if (passes < 1) return CBDG_OK;

@@ -48,12 +48,12 @@ int main()
             long long limit;
             if (scanf("%d %d %d %d %d %d %lld", &Lx, &Ly, &bcx, &bcy, &Bt, &f32, &limit) != 7) return 1;
             const cbdg_op op = make_op(Lx, Ly, bcx, bcy, 0, 0);
-            const PipePlan p = pipe_plan(&op, Bt, f32, limit);
+            const PipePlan p = pipe_plan(&op, Bt, 20000, f32, limit);
             launched_W = launched_C = 0;
             if (!p.W) { printf("none\n"); continue; }
             static char ws[1];
             double mu[2];
-            if (run_pipe(&op, p, f32, nullptr, Bt, 100, ws, mu, mu, true, nullptr)) return 2;
+            if (run_pipe(&op, p, f32, nullptr, Bt, 20000, ws, mu, mu, true, nullptr)) return 2;
             printf("%d %d %d %d %d %lld\n", p.W, p.L, p.segs, launched_W, launched_C, (long long)p.bytes);
         } else if (!strcmp(what, "route")) {
             int cplx, general, N, direct;
@@ -63,7 +63,7 @@ int main()
             if (cbdg_moments_workspace_size(&op, Bt, f32 ? CBDG_FP32_ACC64 : CBDG_FP64, CBDG_ALG_DOUBLING, &bytes)) return 2;
             const int64_t room = direct ? 2 * op.L2 * lane_stride(Bt) * (cplx ? 4 : 2) * (f32 ? 4 : 8) : (int64_t)bytes;
             const char *r = "steps";
-            if (!direct && pipe_plan(&op, Bt, f32, room).W) r = "vpipe";
+            if (!direct && pipe_plan(&op, Bt, N, f32, room).W) r = "vpipe";
             else if (gpipe_plan(&op, Bt, N, f32, direct, room).W) r = "gpipe";
             else if (!direct && gstep_plan(&op, Bt, N, f32, room)) r = "gstep";
             printf("%s\n", r);

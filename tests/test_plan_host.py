@@ -53,3 +53,18 @@ def test_the_planned_shape_is_launched(ask, f32):
         assert 64 * lW * (lC - 1) < c[0] <= 64 * lW * lC, (c, plan)
         seen.add((lW, lC))
     assert len(seen) == (4 if f32 else 6)
+
+
+def test_calls_take_the_faster_passes(ask):
+    """Calls measured on either side of the line, by at least a fifth: few
+    steps in a pass of many, few rows, a part of the GPU filled; and the ones
+    that the pipeline is for."""
+    call = "route %d %d %d %d 0 0 %d %d %d 0"  # Lx Ly bc_x bc_y Bt N f32
+    steps = [(256, 6, 0, 0, 1024, 256, 0), (128, 64, 1, 1, 1024, 48, 0), (128, 300, 0, 0, 1024, 48, 0), (64, 80, 1, 1, 1024, 48, 0),
+             (256, 96, 0, 0, 1024, 48, 1), (256, 3, 0, 0, 700, 256, 1), (200, 8, 1, 1, 1024, 12, 0), (130, 16, 1, 1, 1024, 5, 1),
+             (390, 8, 1, 1, 1024, 5, 0), (256, 256, 0, 0, 64, 256, 1), (24, 128, 1, 1, 1024, 256, 1)]
+    pipe = [(256, 256, 0, 0, 1024, 1024, 0), (256, 256, 0, 0, 1024, 2048, 1), (16, 16, 0, 0, 256, 256, 0), (96, 72, 1, 1, 1024, 384, 0),
+            (150, 100, 0, 0, 441, 2048, 0), (400, 500, 0, 1, 64, 2000, 0), (128, 128, 0, 0, 1024, 512, 0), (64, 64, 1, 1, 1024, 512, 0),
+            (128, 24, 0, 0, 128, 512, 0), (33, 130, 1, 1, 1024, 200, 1), (24, 8, 1, 1, 8, 200, 1)]
+    for calls, want in ((steps, "steps"), (pipe, "vpipe")):
+        assert ask([call % c for c in calls]) == [want] * len(calls)
