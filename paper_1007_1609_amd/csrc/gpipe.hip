@@ -52,16 +52,21 @@ __global__ void k_gpipe_records(const OnSite<T> *__restrict__ ons, const void *_
     }
 }
 
-// Steps of a pass.
-static int gpipe_steps(int W, bool f32, bool cp, bool gen)
+// Steps of a pass, its trips beside its rows, and those until the last stage has finished.
+struct GPipePass { int steps, lead, drain; };
+static GPipePass gpipe_pass(int W, bool f32, bool cp, bool gen)
 {
-    auto shape = [&](auto t, auto c, auto g) -> int {
+    auto shape = [&](auto t, auto c, auto g) -> GPipePass {
         using T = decltype(t);
         constexpr bool CP = decltype(c)::value, GEN = decltype(g)::value;
+        auto of = [](auto sh) -> GPipePass {
+            constexpr int K = decltype(sh)::K, S = decltype(sh)::S;
+            return GPipePass{K * S, K + kCoefAhead<K> + kRound<K>, kPipeAhead + (S - 1) * (K + 1) + 2 * kRound<K>};
+        };
         switch (W) {
-        case 1: return GPipeShape<T, CP, GEN, 1>::K * GPipeShape<T, CP, GEN, 1>::S;
-        case 2: return GPipeShape<T, CP, GEN, 2>::K * GPipeShape<T, CP, GEN, 2>::S;
-        default: return GPipeShape<T, CP, GEN, 3>::K * GPipeShape<T, CP, GEN, 3>::S;
+        case 1: return of(GPipeShape<T, CP, GEN, 1>{});
+        case 2: return of(GPipeShape<T, CP, GEN, 2>{});
+        default: return of(GPipeShape<T, CP, GEN, 3>{});
         }
     };
     using yes = std::true_type;
@@ -72,35 +77,72 @@ static int gpipe_steps(int W, bool f32, bool cp, bool gen)
                      : (gen ? shape(0., no{}, yes{}) : shape(0., no{}, no{})));
 }
 
-// Whether the pipeline is the faster way, by the time of either (us).  Here:
-// trips of a workgroup's vectors, 1.1 us each, more where rows wrap and with two
-// workgroups on a CU.  The one-step kernels: per step a launch (under doubling
-// with its reductions; nearly all latency on small tiles) and the tile's bytes.
-// Over 490 calls of 3 to 192 columns, 3 to 200 rows, 1 to 1024 vectors and N = 24
-// to 260 the middle 80 % of the times lie within 30 % of these.  It is the
-// neighbour moments of periodic-y lattices that stay: the workspace holds two
-// buffers a vector, the pipeline needs four of every workgroup's, and half of the
-// tile has to wait (FP64, N = 260: 11x200, 100 vectors 2.4 ms there, 11.6 here;
-// 34x80, N = 64, 1024 vectors 0.96 / 3.5; under doubling it is faster in 19 of 20
-// calls, 2.1 times on average).
-static bool gpipe_pays(const cbdg_op *op, const GPipePlan &p, int Bt, int N, bool f32, bool direct)
+// Whether the pipeline is the faster way, by a tenth at least, by the time of
+// either (us).  Here: trips of a workgroup's vectors, more where rows wrap and with
+// two workgroups on a CU.  The other kernels: launches (nearly all latency on small
+// tiles) and the bytes of the tile.  Timed over 3600 calls of 3 to 400 columns, 2
+// to 200 rows, 1 to 1024 vectors and N = 5 to 260.
+//
+// Neighbour moments: 1.27 times faster than with the one-step kernels alone, one
+// call in 100 a tenth or more slower (25 us in place of 35: one in 70).  It is
+// those of periodic-y lattices that stay there: the workspace holds two buffers a
+// vector, the pipeline needs four of every workgroup's, and half of the tile has
+// to wait (FP64, N = 260: 11x200, 100 vectors 2.4 ms there, 11.6 here; 34x80, N =
+// 64, 1024 vectors 0.96 / 3.5).
+static bool gpipe_pays_direct(const cbdg_op *op, const GPipePlan &p, int Bt, int N, bool f32)
 {
     const bool cp = op->scalar == CBDG_COMPLEX, gen = op->general;
-    const int L = gpipe_steps(p.W, f32, cp, gen), M = direct ? N - 1 : N / 2;
+    const int L = gpipe_pass(p.W, f32, cp, gen).steps, M = N - 1;
     int64_t trips = 0;
     for (int n = 2; n <= M; n += L) {
         const int64_t cone = 2 * (int64_t)(n + L - 1) + 1;
         const int64_t rows = cone < op->Ly ? cone : op->Ly + (op->bc_y ? 2 * L : 0);
         trips += std::max<int64_t>(rows + L / 4 + 8, L + 12);
     }
-    const double trip = (direct ? 1.15 : 1.1) * (op->bc_x || op->bc_y ? (direct ? 1.45 : 1.25) : 1.0) * (p.grid > 256 ? 1.35 : 1.0);
-    const double here = 25.0 + (double)(trips * ceil_div(Bt, p.grid)) * trip;
+    const double trip = 1.15 * (op->bc_x || op->bc_y ? 1.45 : 1.0) * (p.grid > 256 ? 1.35 : 1.0);
+    const double here = 35.0 + (double)(trips * ceil_div(Bt, p.grid)) * trip;
     const int kind = gen ? (cp ? 2 : 1) : 0;
-    static const double kLaunch[2][3] = {{14, 15, 16}, {8, 12, 13}};  // us a step
-    static const double kRate[3] = {2.2e6, 1.9e6, 1.6e6};             // bytes of one vector a us
-    const double launch = kLaunch[direct][kind] * (op->Ly < 8 ? 0.75 : 1.0);
+    static const double kLaunch[3] = {8, 12, 13};          // us a step
+    static const double kRate[3] = {2.2e6, 1.9e6, 1.6e6};  // bytes of one vector a us
     const double bytes = (double)op->L2 * (double)lane_stride(Bt) * (cp ? 4 : 2) * (f32 ? 4 : 8);
-    return here <= 0.9 * (20.0 + M * (launch + bytes / kRate[kind]));
+    return here <= 0.9 * (20.0 + M * (kLaunch[kind] * (op->Ly < 8 ? 0.75 : 1.0) + bytes / kRate[kind]));
+}
+
+// Doubling: 2.2 times faster than with the other kernels alone, no call of 1200 a
+// tenth slower.  Bytes and sites are those inside the cones, the tile's start
+// sites taken to lie in a run; rows beside a workgroup's own take no sums.
+static bool gpipe_pays_doubling(const cbdg_op *op, const GPipePlan &p, int Bt, int N, bool f32, int64_t room)
+{
+    const bool cp = op->scalar == CBDG_COMPLEX, gen = op->general;
+    const int kind = (cp ? 1 + gen : 0), M = N / 2;  // per bond, complex, both
+    static const double kTrip[3][2] = {{1.02, 1.09}, {1.14, 1.25}, {1.24, 1.38}};  // FP64, FP32
+    const GPipePass s = gpipe_pass(p.W, f32, cp, gen);
+    const int64_t Ly = op->Ly, L = s.steps;
+    double trips = s.drain;
+    for (int64_t n = 2; n <= M; n += L) {
+        const int64_t cone = 2 * (n + L - 1) + 1, own = std::min(Ly, cone);
+        const int64_t t = std::max(own + (op->bc_y && cone >= Ly ? 2 * L : 0) + s.lead, L + 10);
+        trips += (double)t - 0.34 * (double)(t - own);
+    }
+    const double two = p.grid > 256 ? 1.19 : 1.0;
+    const int full = Bt / p.grid, rest = Bt % p.grid;
+    const double here = 23.0 + trips * (full * two + (rest ? (rest > 256 ? two : 1.0) : 0.0)) * kTrip[kind][f32] *
+                                   (p.W > 1 ? 1.07 : 1.0) * (op->bc_x ? 1.25 : 1.0) * (op->bc_y ? 1.28 : 1.0);
+    static const double kLaunch[3] = {16.5, 13.5, 17.0};   // us a step, with its reductions
+    static const double kRate[3] = {1.6e6, 1.8e6, 1.6e6};  // bytes of one vector a us
+    // FP32 strips of four and eight complex columns take half as long again
+    const double launch = kLaunch[kind] * (Ly < 8 ? 0.76 : 1.0) * (f32 && cp && op->Lx % 4 == 0 ? 1.6 : 1.0);
+    const double row = (double)op->Lx * (double)lane_stride(Bt) * (cp ? 4 : 2) * (f32 ? 4 : 8);
+    double rows = 2.0 * (double)Ly, sites = 0.0;  // cleared, written by the first step
+    for (int64_t n = 1; n <= M; ++n) {
+        rows += (double)(op->bc_y ? Ly : std::min(Ly, ceil_div(Bt, op->Lx) + 2 * n));
+        sites += (double)std::min<int64_t>(op->L2, 2 * n * n);
+    }
+    double there = 30.0 + M * launch + rows * row / kRate[kind];
+    // the steps inside each vector's cone: nearly all launches
+    if (gstep_plan(op, Bt, N, f32, room))
+        there = std::min(there, 20.0 + 20.0 * M + sites * Bt * ((gen ? (cp ? 20 : 12) : 4) + (cp ? 12 : 6)) * (f32 ? 4 : 8) / 14e6);
+    return here <= 0.9 * there;
 }
 
 GPipePlan gpipe_plan(const cbdg_op *op, int Bt, int N, bool f32, bool direct, int64_t room)
@@ -129,7 +171,7 @@ GPipePlan gpipe_plan(const cbdg_op *op, int Bt, int N, bool f32, bool direct, in
     p.buf_at = recs;
     p.nbuf = nbuf;
     p.W = W;
-    if (!gpipe_pays(op, p, Bt, N, f32, direct)) p.W = 0;
+    if (!(direct ? gpipe_pays_direct(op, p, Bt, N, f32) : gpipe_pays_doubling(op, p, Bt, N, f32, room))) p.W = 0;
     return p;
 }
 
@@ -179,7 +221,7 @@ int run_gpipe(const cbdg_op *op, const GPipePlan &p, bool f32, const int32_t *si
     A.sites = sites; A.mu_ee = mu_ee; A.mu_he = mu_he;
     G.recs = p.recs; G.nb_ee = nb_ee; G.nb_he = nb_he;
     const int steps = nb_ee ? N - 2 : N / 2 - 1;
-    A.n_pass = steps > 0 ? (int)ceil_div(steps, gpipe_steps(p.W, f32, cp, gen)) : 0;
+    A.n_pass = steps > 0 ? (int)ceil_div(steps, gpipe_pass(p.W, f32, cp, gen).steps) : 0;
     if (f32) {
         if (cp) return gen ? launch_gpipe_f32_cg(G, p.grid, st) : launch_gpipe_f32_cu(G, p.grid, st);
         return gen ? launch_gpipe_f32_rg(G, p.grid, st) : launch_gpipe_f32_ru(G, p.grid, st);

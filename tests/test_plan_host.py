@@ -68,3 +68,14 @@ def test_calls_take_the_faster_passes(ask):
             (128, 24, 0, 0, 128, 512, 0), (33, 130, 1, 1, 1024, 200, 1), (24, 8, 1, 1, 8, 200, 1)]
     for calls, want in ((steps, "steps"), (pipe, "vpipe")):
         assert ask([call % c for c in calls]) == [want] * len(calls)
+
+
+def test_general_calls_take_the_faster_passes(ask):
+    """The same for complex and per-bond operators and neighbour moments."""
+    call = "route %d %d %d %d %d %d %d %d %d %d"  # Lx Ly bc_x bc_y complex per-bond Bt N f32 neighbours
+    steps = [(11, 130, 1, 1, 0, 0, 100, 5, 0, 1), (16, 130, 1, 1, 1, 1, 512, 260, 0, 1), (11, 60, 1, 0, 0, 0, 512, 5, 0, 1),
+             (95, 3, 0, 1, 1, 0, 285, 12, 0, 1), (47, 7, 1, 0, 0, 0, 100, 5, 1, 1), (33, 12, 1, 0, 1, 1, 250, 5, 1, 0)]
+    pipe = [(48, 40, 0, 0, 1, 1, 1024, 256, 0, 1), (48, 40, 0, 0, 1, 1, 512, 256, 0, 0), (41, 20, 0, 0, 1, 0, 40, 256, 0, 1),
+            (65, 9, 1, 1, 1, 1, 30, 100, 0, 1)]
+    for calls, want in ((steps, "steps"), (pipe, "gpipe")):
+        assert ask([call % c for c in calls]) == [want] * len(calls)
