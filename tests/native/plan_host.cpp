@@ -4,6 +4,8 @@
 //
 //   launch Lx Ly bc_x bc_y Bt f32 limit   the pipelined plan within `limit`
 //       bytes and what it launches: "W L segs" and the launched "W C" (or "none")
+//   prefix Lx Ly bc_x bc_y Bt N           "done at": the steps that the forward part
+//       of a reverse pass takes in the pipeline and the buffer pair they end in
 //   route Lx Ly bc_x bc_y complex general Bt N f32 direct
 //       "vpipe", "gpipe", "gstep" or "steps"
 #include "step.hpp"
@@ -55,6 +57,15 @@ int main()
             double mu[2];
             if (run_pipe(&op, p, f32, nullptr, Bt, 20000, ws, mu, mu, true, nullptr)) return 2;
             printf("%d %d %d %d %d %lld\n", p.W, p.L, p.segs, launched_W, launched_C, (long long)p.bytes);
+        } else if (!strcmp(what, "prefix")) {
+            int N, done = 0, at = 0;
+            if (scanf("%d %d %d %d %d %d", &Lx, &Ly, &bcx, &bcy, &Bt, &N) != 6) return 1;
+            const cbdg_op op = make_op(Lx, Ly, bcx, bcy, 0, 0);
+            static char ws[4];
+            void *const buf[4] = {ws, ws + 1, ws + 2, ws + 3};
+            double mu[2];
+            if (run_pipe_prefix(&op, nullptr, Bt, N, N / 2, buf, ws, mu, mu, &done, &at, nullptr)) return 2;
+            printf("%d %d\n", done, at);
         } else if (!strcmp(what, "route")) {
             int cplx, general, N, direct;
             if (scanf("%d %d %d %d %d %d %d %d %d %d", &Lx, &Ly, &bcx, &bcy, &cplx, &general, &Bt, &N, &f32, &direct) != 10) return 1;

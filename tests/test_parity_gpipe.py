@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import workloads as W
-from tests.gpu_common import DEV, gpu_moments, maxdiff
+from tests.gpu_common import DEV, TOL_MOMENT, gpu_moments, maxdiff
 
 pytestmark = pytest.mark.gpu
 
@@ -100,3 +100,59 @@ def test_neighbour_moments_of_two_open_rows(Lx, bcx, kind, precision, tol):
     op.close()
     o_ee, o_he = oracle.neighbour_moments(oracle.workload_csr(w, a, b), Lx, 2, bcx, 0, w.start_sites, w.N)
     assert maxdiff(nb_ee, o_ee) <= tol and maxdiff(nb_he, o_he) <= tol
+
+
+# Neighbour moments whose passes wrap or close rows, or take two columns a lane,
+# with the kinds (index into KINDS, 3 + 1: real uniform) and precisions that the
+# library gives to the row pipeline; tests/test_plan_host.py checks that it does.
+_ALL = [(k, p) for k in range(5) for p in (0, 1)]
+NB_ROUTED = [
+    (65, 9, 0, 1, 30, 90, _ALL), (65, 9, 1, 1, 30, 90, _ALL), (128, 10, 1, 1, 30, 90, _ALL), (128, 10, 1, 0, 60, 90, _ALL),
+    (64, 12, 1, 0, 60, 90, _ALL), (48, 40, 1, 0, 30, 100, _ALL), (100, 24, 1, 0, 60, 100, _ALL),
+    # more rows than two passes' halo
+    (48, 40, 0, 1, 12, 100, [(4, 0), (3, 0), (1, 0), (2, 0), (3, 1), (0, 1), (1, 1), (2, 1)]),
+    (64, 61, 1, 1, 6, 150, [(3, 1), (1, 1)]),
+]
+
+
+@pytest.mark.parametrize("case,kind,precision", [(c[:6], k, p) for c in NB_ROUTED for k, p in c[6]])
+def test_routed_neighbour_moments_match_oracle(case, kind, precision):
+    import oracle
+    import paper_1007_1609_amd as P
+    Lx, Ly, bcx, bcy, n, N = case
+    w = _workload(Lx, Ly, N, bcx, bcy, (KINDS + [(False, False, 0.0)])[kind], n)
+    sites = w.start_sites.copy()
+    sites[:6] = [0, Lx - 1, Lx * Ly - 1, Lx * (Ly - 1), Lx, Lx * Ly - 2]
+    op = P.Operator.from_workload(w, DEV)
+    out = P.chebyshev_moments_nb(op, torch.as_tensor(sites, device=DEV), N, n, precision)
+    ee, he, nb_ee, nb_he = (t.cpu().numpy() for t in out)
+    a, b = op.bounds.a, op.bounds.b
+    op.close()
+    tol = 2e-5 if precision else TOL_MOMENT
+    o_ee, o_he = oracle.neighbour_moments(oracle.workload_csr(w, a, b), Lx, Ly, bcx, bcy, sites, N)
+    assert maxdiff(nb_ee, o_ee) <= tol and maxdiff(nb_he, o_he) <= tol
+    l_ee, l_he = oracle.workload_moments(w, a, b, sites=sites)
+    assert maxdiff(ee, l_ee) <= tol and maxdiff(he, l_he) <= tol
+
+
+# Doubling: (Lx, Ly, bc_x, bc_y, vectors, N, kinds of KINDS in FP64 and FP32 that take the pipeline)
+DOUBLING_ROUTED = [
+    (1, 9, 0, 0, 9, 80, (0, 1, 3), (0, 1, 3)), (3, 3, 1, 1, 9, 81, (0, 1, 3), (0, 1, 3)), (63, 12, 0, 1, 150, 80, (0, 1, 3), (0, 1, 3)),
+    (64, 9, 1, 0, 150, 120, (0, 1, 3), (0,)), (65, 14, 1, 1, 150, 80, (0, 1, 3), (0, 1, 3)), (128, 7, 0, 0, 150, 121, (0, 1, 3), (0,)),
+    (129, 6, 0, 1, 150, 80, (), (0, 1, 3)), (40, 61, 1, 1, 150, 121, (0, 1, 3), (0,)), (127, 20, 0, 1, 150, 120, (0, 1, 3), (0, 1, 3)),
+    (33, 48, 0, 1, 100, 160, (0, 1, 3), (0, 1, 3)),
+]
+
+
+@pytest.mark.parametrize("case,kind,precision", [(c[:6], k, p) for c in DOUBLING_ROUTED for p in (0, 1) for k in c[6 + p]])
+def test_routed_doubling_matches_oracle(case, kind, precision):
+    import oracle
+    Lx, Ly, bcx, bcy, n, N = case
+    w = _workload(Lx, Ly, N, bcx, bcy, KINDS[kind], n)
+    op, ee, he = gpu_moments(w, N=N, tile=n, precision=precision, algorithm=2)
+    a, b = op.bounds.a, op.bounds.b
+    op.close()
+    few = slice(None, None, max(1, len(w.start_sites) // 12))
+    o_ee, o_he = oracle.workload_moments(w, a, b, sites=w.start_sites[few])
+    tol = 2e-5 if precision else TOL_MOMENT
+    assert maxdiff(ee[few], o_ee) <= tol and maxdiff(he[few], o_he) <= tol

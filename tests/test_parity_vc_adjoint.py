@@ -200,3 +200,33 @@ def test_benchmark_lattice_matches_checkpoints():
     rd = float((gd - cd).abs().max() / cd.abs().max())
     print("256x256 N=%d: rel diff eps %.2e delta %.2e" % (N, re, rd))
     assert re < 1e-9 and rd < 1e-9
+
+
+# Periodic y with more rows than the last passes' cones (full passes that take
+# only the rows inside them) and forward parts that begin with whole pipelined
+# passes: (Lx, Ly, bc_x, vectors, N, steps taken there, buffer pair they end in);
+# tests/test_plan_host.py checks the last two.
+PERIODIC = [
+    (64, 41, 0, 40, 64, 21, 2), (64, 41, 1, 40, 90, 41, 0), (64, 57, 1, 200, 130, 61, 2),
+    (128, 41, 0, 40, 65, 21, 2), (128, 57, 1, 40, 111, 41, 0), (256, 41, 0, 40, 64, 25, 2), (256, 41, 1, 40, 110, 49, 0),
+    (64, 41, 0, 300, 52, 0, 0), (256, 41, 1, 300, 64, 0, 0),
+]
+
+
+@pytest.mark.parametrize("Lx,Ly,bcx,n,N,done,at", PERIODIC)
+def test_tall_periodic_lattices(Lx, Ly, bcx, n, N, done, at):
+    w = W.small_random(Lx, Ly, N=N, seed=Lx + N, bc_x=bcx, bc_y=1, n_sites=n)
+    sites = w.start_sites.copy()
+    sites[:4] = [0, Lx - 1, Lx * Ly - 1, Lx * (Ly - 1)]
+    rng = np.random.default_rng(N)
+    dee, dhe = rng.normal(size=(n, N)), rng.normal(size=(n, N))
+    # all start vectors against the checkpointed pass, a few against the oracle
+    ge, gd, a, b = _backward(w, N, dee, dhe, n, REV, sites=sites)
+    ce, cd, _, _ = _backward(w, N, dee, dhe, n, 0, sites=sites)
+    assert _rel(ge, ce) < 1e-11 and _rel(gd, cd) < 1e-11
+    few = np.r_[0:4, 4:n:max(1, n // 6)]
+    d2, h2 = np.zeros_like(dee), np.zeros_like(dhe)
+    d2[few], h2[few] = dee[few], dhe[few]
+    ge, gd, _, _ = _backward(w, N, d2, h2, n, REV, sites=sites)
+    oe, od = oracle.moments_backward(oracle.workload_csr(w, a, b), sites[few], N, dee[few], dhe[few])
+    assert _rel(ge, oe) < 1e-10 and _rel(gd, od) < 1e-10

@@ -79,3 +79,27 @@ def test_general_calls_take_the_faster_passes(ask):
             (65, 9, 1, 1, 1, 1, 30, 100, 0, 1)]
     for calls, want in ((steps, "steps"), (pipe, "gpipe")):
         assert ask([call % c for c in calls]) == [want] * len(calls)
+
+
+def test_the_parity_tests_reach_the_pipelines(ask):
+    from tests import test_parity_gpipe as G
+    from tests import test_parity_pipe as V
+    kinds = [(int(c), int(b)) for c, b, _ in G.KINDS] + [(0, 0)]
+    call = "route %d %d %d %d %d %d %d %d %d %d"
+    nb = [call % (*c[:4], *kinds[k], c[4], c[5], p, 1) for c in G.NB_ROUTED for k, p in c[6]]
+    dbl = [call % (*c[:4], *kinds[k], min(c[4], c[0] * c[1]), c[5], p, 0) for c in G.DOUBLING_ROUTED for p in (0, 1) for k in c[6 + p]]
+    for calls in (nb, dbl):
+        assert [(c, r) for c, r in zip(calls, ask(calls)) if r != "gpipe"] == []
+    real = [(Lx, 31, bcx, Lx % 2, min(260, 31 * Lx), 90, p) for Lx in V.WIDTHS for bcx in (0, 1) for p in (0, 1) if not bcx or Lx >= 3]
+    real += [(Lx, 40, 0, 0, 257, 2 * (k * L + 1) + off, 0) for Lx, L in ((64, 20), (192, 24), (384, 12)) for k in (1, 2)
+             for off in (-2, -1, 0, 1, 2, 3)]
+    real += [(*c, 161, p) for c in ((64, 200, 0, 0, 3), (64, 200, 0, 1, 3), (100, 150, 1, 1, 20), (256, 130, 0, 0, 1), (300, 90, 0, 1, 9),
+                                    (16, 3, 1, 1, 48), (64, 61, 0, 1, 300), (128, 43, 1, 1, 300)) for p in (0, 1)]
+    calls = [call % (*c[:4], 0, 0, *c[4:], 0) for c in real]
+    assert [(c, r) for c, r in zip(calls, ask(calls)) if r != "vpipe"] == []
+
+
+def test_the_reverse_pass_tests_begin_in_the_pipeline(ask):
+    from tests.test_parity_vc_adjoint import PERIODIC
+    calls = ["prefix %d %d %d 1 %d %d" % c[:5] for c in PERIODIC]
+    assert ask(calls) == ["%d %d" % c[5:] for c in PERIODIC]
