@@ -99,6 +99,7 @@ static bool gpipe_pays_direct(const cbdg_op *op, const GPipePlan &p, int Bt, int
         const int64_t rows = cone < op->Ly ? cone : op->Ly + (op->bc_y ? 2 * L : 0);
         trips += std::max<int64_t>(rows + L / 4 + 8, L + 12);
     }
+    if (trips > kMaxTrips) return false;
     const double trip = 1.15 * (op->bc_x || op->bc_y ? 1.45 : 1.0) * (p.grid > 256 ? 1.35 : 1.0);
     const double here = 35.0 + (double)(trips * ceil_div(Bt, p.grid)) * trip;
     const int kind = gen ? (cp ? 2 : 1) : 0;
@@ -124,6 +125,7 @@ static bool gpipe_pays_doubling(const cbdg_op *op, const GPipePlan &p, int Bt, i
         const int64_t t = std::max(own + (op->bc_y && cone >= Ly ? 2 * L : 0) + s.lead, L + 10);
         trips += (double)t - 0.34 * (double)(t - own);
     }
+    if (trips > (double)kMaxTrips) return false;
     const double two = p.grid > 256 ? 1.19 : 1.0;
     const int full = Bt / p.grid, rest = Bt % p.grid;
     const double here = 23.0 + trips * (full * two + (rest ? (rest > 256 ? two : 1.0) : 0.0)) * kTrip[kind][f32] *

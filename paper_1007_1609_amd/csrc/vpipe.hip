@@ -131,6 +131,7 @@ static double pipe_time(const cbdg_op *op, const PipePlan &p, const PipeWidth &w
         halo += (double)(t - own);
     }
     if (p.segs == 1) trips += w.drain;
+    if (p.segs == 1 && trips > (double)kMaxTrips) return HUGE_VAL;
     trips -= (f32 ? 0.25 : 0.1) * halo;
     double trip = (double)(nb / slots) * (w.per_cu == 2 ? w.two : w.one);
     if (nb % slots) trip += w.per_cu == 2 && nb % slots > 256 ? w.two : w.one;

@@ -335,6 +335,10 @@ template <typename T, int W, int C> struct PipeShape {
 // Trips from the load of a row to the trip that stage 0 uses it on.
 constexpr int kPipeAhead = 3;
 
+// Most trips of a launch that are planned (a workgroup counts them in an int;
+// half of what it holds).  10^9 trips take a quarter of an hour.
+constexpr int64_t kMaxTrips = 1 << 30;
+
 template <typename T, int W, int C, int K, int S, int XM, bool SEG, bool FOLD>
 __global__ __launch_bounds__(S * C * kWave) __attribute__((amdgpu_waves_per_eu(PipeShape<T, W, C>::waves)))
 void k_vpipe(PipeArgs A)

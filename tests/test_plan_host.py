@@ -103,3 +103,10 @@ def test_the_reverse_pass_tests_begin_in_the_pipeline(ask):
     from tests.test_parity_vc_adjoint import PERIODIC
     calls = ["prefix %d %d %d 1 %d %d" % c[:5] for c in PERIODIC]
     assert ask(calls) == ["%d %d" % c[5:] for c in PERIODIC]
+
+
+def test_calls_of_more_trips_than_an_int_counts(ask):
+    """A long recursion on a long strip (hours of work): its trips overflowed
+    the kernel's count, and nothing beyond the first moments was written."""
+    call = "route 8 1000000 0 0 1 0 512 %d 0 1"
+    assert ask([call % 20000, call % 200000]) == ["gpipe", "steps"]
