@@ -27,7 +27,9 @@ tile's seed and coefficient kernels are charged to the recursion launches):
 and output vectors of its passes inside their light cones -- over the average
 launch duration; `effective_GBps` counts instead the bytes of the plain one-step
 recursion streamed over the whole lattice, which the multi-step passes and
-the light cone avoid.  `traffic` is the HBM traffic per launch from the
+the light cone avoid.  `bound` names the roof that these bytes are priced
+against; the row pipeline itself stays below it, at its vector instructions
+and barriers.  `traffic` is the HBM traffic per launch from the
 rocprofv3 counters stored under profiles/ (null when they were taken on a
 different kernel source).  `precision_form` runs the FP32-recursion form
 (FP64 moment sums) and the FP64 path at N = 2048 on the same 16 tiles;

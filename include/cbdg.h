@@ -185,9 +185,9 @@ int cbdg_moments_workspace_size(const cbdg_op *op, int32_t tile, int32_t precisi
  * The start vectors are processed in tiles of `tile` vectors; all tiles run
  * inside this call.  Under DOUBLING real operators with uniform hopping (up
  * to 512 columns), and complex and per-bond ones on narrower lattices, store a
- * tile vector by vector and run many recursion steps per launch, each vector
- * clipped to its own light cone; the site values and doubling sums agree with
- * those of the other passes to rounding.
+ * tile vector by vector and run many recursion steps per launch where that is
+ * the faster way, each vector clipped to its own light cone; the site values and
+ * doubling sums agree with those of the other passes to rounding.
  *   start_sites  [n_start] int32 lattice sites (duplicates allowed)
  *   n_start      >= 0 (0: nothing is done)
  *   N            number of moments, >= 1

@@ -10,9 +10,11 @@
 // stage needs no other site's coefficients; columns past the row's end have
 // zero records.  Rows outside the pass are skipped and set to zero.
 //
-// What bounds it: per-bond complex128 takes about 80 operations per site and
-// step against 96 bytes of vectors in the one-step passes, which stream at
-// 5 TB/s; with L steps per crossing the FP64 issue rate bounds it instead.
+// What bounds it: per-bond complex128 takes 96 operations per site and step
+// beside its sums, against 96 bytes of vectors in the one-step passes, which
+// stream at 5 TB/s; with L steps per crossing HBM is at 0.9 TB/s (48x40 neighbour
+// moments), the vector units are busy 45 % of the time, and the rest waits for the
+// records (160 bytes a site, from L2 into registers on every trip) and the barrier.
 //
 // The workgroups are persistent (vector b, then b + gridDim.x, ..): each owns
 // its buffers in the workspace, which hold the vectors of the workgroups in

@@ -162,7 +162,8 @@ struct PipeArgs {
     char *buf;
     int64_t one;
     int flip, cur;
-    const void *coef;    // (2 de, 2 Delta/a) per site in the same row layout
+    const void *coef;    // (de, Delta/a) per site in the same row layout, doubled where the
+                         // recursion folds the factor 2 in (the 64, 128 and 256 columns of vc_width)
     const void *onsite;  // OnSite<T>[L2]
     double th;           // t/a
     double lim;          // moments beyond it are stored as NaN

@@ -13,11 +13,16 @@
 // one before it (the row it needs ahead was written to LDS on the trip
 // before), one barrier per trip.
 //
-// What bounds it: the FP64 issue rate (18 operations per site and step: six
-// additions, six fused multiply-adds of the stencil, six of the doubling
-// sums).  One wavefront per vector and seven steps per launch, as the passes
-// of vcstep.hip run it, is bound by HBM instead (4 vectors per 7 steps at
-// 5 TB/s); here the vectors cross memory 4 times per L >= 16 steps.
+// What bounds it: vector instructions (18 operations per site and step where
+// the factor 2 is folded in, 20 elsewhere: additions and fused multiply-adds of
+// the stencil, six of the doubling sums) and, where wavefronts are few or rows
+// take two, the trip's barrier.  Vector units busy: 256x256 FP32 94 % of the
+// time, FP64 59, 96x72 periodic 76 (a part of it selects and lane reads where
+// rows close), 150x100 54, 400x500 34; HBM 0.8 to 1.4 TB/s.  One wavefront per
+// vector and seven steps per launch, as the passes of vcstep.hip run it, is
+// bound by HBM instead (4 vectors per 7 steps at 5 TB/s); here the vectors cross
+// memory 4 times per L = 12, 20 or 24 steps (two wavefronts a row, rows of up to
+// 8 registers, wider rows).
 //
 // The passes of a vector follow each other inside one launch: rows of pass
 // p + 1 enter as soon as stage 0 has finished pass p, while later stages
@@ -641,7 +646,7 @@ void k_vpipe(PipeArgs A)
                         if constexpr (C > 1) s[k] += sums[stg][1][3 * lane + k];
                     }
                     // (two halves: the registers a fresh read takes cost more,
-                    // 512x512, N = 512: 43.5 ms against 49.6)
+                    // 512x512, N = 512, factor 2 folded in: 43.5 ms against 49.6)
                     PipeArgs B;
                     if constexpr (C > 1) B = A;
                     else B = cold_args<PipeArgs>();
