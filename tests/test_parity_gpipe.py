@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import workloads as W
-from tests.gpu_common import DEV, TOL_MOMENT, gpu_moments, maxdiff
+from tests.gpu_common import DEV, gpu_moments, maxdiff
 
 pytestmark = pytest.mark.gpu
 
@@ -101,6 +101,8 @@ def test_neighbour_moments_of_two_open_rows(Lx, bcx, kind, precision, tol):
     o_ee, o_he = oracle.neighbour_moments(oracle.workload_csr(w, a, b), Lx, 2, bcx, 0, w.start_sites, w.N)
     assert maxdiff(nb_ee, o_ee) <= tol and maxdiff(nb_he, o_he) <= tol
 
+
+from tests.gpu_common import TOL_MOMENT  # noqa: E402
 
 # Neighbour moments whose passes wrap or close rows, or take two columns a lane,
 # with the kinds (index into KINDS, 3 + 1: real uniform) and precisions that the
